@@ -210,7 +210,7 @@ size_t step_workspace(const StepPlan &p, int batch, int hq, int hkv, int lq) {
 
 ws::TileShape plan_prefill(int) { return default_shape(); }
 
-// Backward workspace: (lse * log2 e, <dO, O>) per row as f32 pairs, then the
+// Backward workspace: lse * log2 e and -<dO, O> of every row (f32), then the
 // key end of each token (int32), at a 256-byte aligned offset.
 size_t bwd_dl_bytes(int batch, int hq, int seq) {
     return ((size_t)batch * hq * seq * 2 * sizeof(float) + 255) / 256 * 256;
@@ -490,6 +490,8 @@ int ws_block_causal_prefill_bwd(ws_tensor4 q, ws_tensor4 k, ws_tensor4 v, ws_ten
     a.dq = (float *)dq.ptr; a.dq_sb = dq.stride_b; a.dq_st = dq.stride_t; a.dq_sh = dq.stride_h;
     a.dk = (float *)dk.ptr; a.dk_sb = dk.stride_b; a.dk_st = dk.stride_t; a.dk_sh = dk.stride_h;
     a.dv = (float *)dv.ptr; a.dv_sb = dv.stride_b; a.dv_st = dv.stride_t; a.dv_sh = dv.stride_h;
+    a.wide_strides = std::max(std::max(q.stride_t, k.stride_t), std::max(v.stride_t, dout.stride_t)) >=
+                     WS_MAX_KV_TOKEN_STRIDE;
     a.dl = (float *)workspace;
     a.kend = (int32_t *)((char *)workspace + bwd_dl_bytes(batch, num_q_heads, seq_len));
     a.B = batch; a.L = seq_len; a.Hq = num_q_heads; a.Hkv = num_kv_heads; a.G = num_q_heads / num_kv_heads;

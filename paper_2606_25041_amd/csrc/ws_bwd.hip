@@ -12,6 +12,7 @@ namespace ws {
 namespace {
 
 constexpr int KB_DKDV = 16;   // key tiles of one group taken together on an XCD (dK/dV)
+constexpr int AH = 2;         // LDS operand reads issued this many MFMAs ahead
 
 // ---------------------------------------------------------------------------
 // Gradients of the whole-sequence path (training shares the causal format,
@@ -59,8 +60,8 @@ __device__ __forceinline__ void tr_bases(int lane, uint32_t (&tb)[2]) {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// Per row: (lse * log2(e), <dO, O>) and, per token, the end of the keys it
-// sees.  LPR lanes per row, 16 bytes each.
+// Per row: lse * log2(e) and -<dO, O> (two rows of L per head), and, per
+// token, the end of the keys it sees.  LPR lanes per row, 16 bytes each.
 template <int D>
 __global__ __launch_bounds__(256) void bwd_prep_kernel(const BwdArgs a) {
     constexpr int LPR = D / 8;
@@ -83,8 +84,9 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const BwdArgs a) {
     for (int m = LPR / 2; m >= 1; m >>= 1) part += __shfl_xor(part, m, LPR);
     if (r < nrows && c == 0) {
         const int64_t idx = ((int64_t)b * a.Hq + h) * a.L + i;
-        a.dl[2 * idx] = a.lse[idx] * 1.4426950408889634f;
-        a.dl[2 * idx + 1] = part;
+        float *dl = a.dl + 2 * ((int64_t)b * a.Hq + h) * a.L + i;
+        dl[0] = a.lse[idx] * 1.4426950408889634f;
+        dl[a.L] = -part;
         if (h == 0) {
             const int32_t *offs = a.offsets + (int64_t)b * (a.nb + 1);
             const int32_t *text = a.text_starts ? a.text_starts + (int64_t)b * a.nb : nullptr;
@@ -147,8 +149,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int k_hi = ld_uniform(kend_b, min(q0 + 127, a.L - 1));
     const int kfull = ld_uniform(kend_b, q0);
     const int my_kend = kend_b[rc];
-    const int64_t ridx = ((int64_t)b * a.Hq + h) * a.L + rc;
-    const float lse2 = a.dl[2 * ridx], Dr = a.dl[2 * ridx + 1];
+    const float *dlr = a.dl + 2 * ((int64_t)b * a.Hq + h) * a.L + rc;
+    const float lse2 = dlr[0], nD = dlr[a.L];
     const float c2 = a.scale_log2;
 
     // B fragments of the lane's query row: q and dO, head dims 16 kk + 8 hf + [0, 8)
@@ -210,7 +212,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 const int key = t * 64 + mb * 32 + 8 * (v >> 2) + 4 * hf + (v & 3);
                 const float p0 = fast_exp2(__builtin_fmaf(S[v], c2, -lse2));
                 const float p = (!need_mask || key < my_kend) ? p0 : 0.f;
-                dsf[v >> 3][v & 7] = (__bf16)(p * (dPt[v] - Dr));
+                dsf[v >> 3][v & 7] = (__bf16)(p * (dPt[v] + nD));
             }
             // dQ^T += K^T dS^T over this half's keys
 #pragma unroll
@@ -244,6 +246,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // from the sequence end) alternate between the two groups, each with its own
 // two LDS stages, so two waves share every SIMD.  At the end group 1 hands its
 // partial sums to group 0 through LDS (fixed order: group 0's + group 1's).
+//
+// A chunk costs a wave 32 MFMAs (1024 cycles) and, as straight code, half
+// as many cycles again of vector work that both waves of a SIMD reach
+// together; so every vector instruction, address step and load stands in the
+// shadow of an MFMA that does not need it (chunk() below), element masks run
+// only on the chunks that straddle a block end, and the loads take
+// wave-uniform bases advanced by additions.  2 x 16384 tokens, GQA 32/8 x
+// 128: 9.0 -> 7.8 ms (cycles -15 %; the clock is power-limited there, 1.74
+// to 1.86 GHz, and MFMA busy 48 -> 59 %).  Two MFMAs of read-ahead and three
+// measured the same.  A barrier per group of four waves instead of the
+// work-group's, with or without a half-step offset between the groups,
+// measured the same too.
 template <int D>
 __global__ __launch_bounds__(512) void bwd_dkdv_kernel(const BwdArgs a) {
     constexpr int ROWB = 2 * D, KK = D / 16, MD = D / 32;
@@ -252,8 +266,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(const BwdArgs a) {
     constexpr int SMEM = 2 * TILEK + 2 * 2 * 2 * TILEC;   // K, V; [group][stage][Q, dO]
     static_assert(2 * 4 * MD * 16 * 64 * 4 <= SMEM, "the partial sums fit the tiles' space");
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
-    __shared__ __attribute__((aligned(16))) float sdl[2][2][2][32];   // [group][stage][lse2, D][row]
-    __shared__ __attribute__((aligned(16))) int skend[2][2][32];
+    __shared__ __attribute__((aligned(256))) float srow[2][2][128];   // [group][stage][lse2, -D, key end (twice) of 32 rows]
     const int nkt = (a.L + 127) / 128;
     const int wid = blockIdx.x;
     // Key tiles from the first keys (seen by the most rows: the heaviest)
@@ -282,7 +295,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(const BwdArgs a) {
     const int b = grpi / a.Hkv;
     const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int grp = wave >> 2, sub = wave & 3, gtid = tid & 255;
+    const int grp = wave >> 2, sub = wave & 3;
     const int kw0 = kt * 128;
     const int key = kw0 + 32 * sub + l32;
     const float c2 = a.scale_log2;
@@ -317,106 +330,200 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(const BwdArgs a) {
     const int total = a.G * nch;            // chunks; group grp takes chunks grp, grp + 2, ...
     const int nstep = (total + 1) / 2;
 
-    float lreg = 0.f, dreg = 0.f;
-    int kreg = 0;
-    auto chunk_base = [&](int it) -> uint32_t { return (uint32_t)(2 * TILEK + ((grp * 2 + (it >> 1 & 1)) * 2) * TILEC); };
-    // the DMA of chunk it (Q and dO rows) and the (lse2, D, key end) of its
-    // rows into registers; group-uniform
-    auto issue_chunk = [&](int it) {
-        const int c = it / a.G, hh = it - c * a.G;
-        const int h = kvh * a.G + hh;
-        const int r0 = a.L - 32 * (c + 1);   // may be negative: such rows are no rows
-        const uint32_t base = lds_addr(smem) + chunk_base(it);
-        dma_rows<D, 4, 32>((const char *)(a.q + b * a.q_sb + h * a.q_sh), 2 * a.q_st, r0, a.L - 1, base, sub, lane);
-        dma_rows<D, 4, 32>((const char *)(a.dout + b * a.do_sb + h * a.do_sh), 2 * a.do_st, r0, a.L - 1,
-                           base + TILEC, sub, lane);
-        if (gtid < 32) {
-            const int r = r0 + gtid;
-            if (r >= 0) {
-                const int64_t idx = ((int64_t)b * a.Hq + h) * a.L + r;
-                lreg = a.dl[2 * idx];
-                dreg = a.dl[2 * idx + 1];
-                kreg = kend_b[r];
-            } else {
-                lreg = 0.f;
-                dreg = 0.f;
-                kreg = 0;   // no key visible
-            }
+    // Rows from im on see every key of this wave, so a chunk whose first row
+    // is at or past im needs no element masks (key ends do not decrease).
+    int im;
+    {
+        const int kl = min(kw0 + 32 * sub + 31, a.L - 1);
+        int mlo = i0, mhi = a.L;
+        while (mlo < mhi) {
+            const int mid = (mlo + mhi) >> 1;
+            if (ld_uniform(kend_b, mid) > kl) mhi = mid; else mlo = mid + 1;
+        }
+        im = mlo;
+    }
+    // Q and dO rows of one chunk go straight to LDS: wave-wide load i of wave
+    // `sub` fills rows 4 RPW i + RPW sub .. + RPW - 1 of the tile, from a
+    // wave-uniform base and a per-lane 32-bit offset (the swizzle repeats
+    // every 16 rows, so the offset serves every i).
+    constexpr int RPW = 1024 / ROWB, LPR = ROWB / 16, NI = TILEC / 4096;
+    static_assert(4 * RPW % 16 == 0, "the swizzle must repeat across a wave's loads");
+    const int64_t qst = 2 * a.q_st, dst = 2 * a.do_st;
+    const int lrow = RPW * sub + lane / LPR;
+    const uint32_t lch = (uint32_t)(16 * ((lane % LPR) ^ swz<D>(lrow)));
+    const uint32_t qofs = (uint32_t)(lrow * (uint32_t)qst) + lch, dofs = (uint32_t)(lrow * (uint32_t)dst) + lch;
+    // lanes 0..31 fetch lse2 and lanes 32..63 -D of the chunk's rows
+    const uint32_t rofs = 4u * (uint32_t)(l32 + hf * a.L), eofs = 4u * (uint32_t)l32;
+    const bool wide = a.wide_strides != 0;   // 32-bit row offsets do not reach
+    // Next chunk to load (this group's chunks are grp, grp + 2, ...): its
+    // first row (may be negative: rows before 0 are no rows), its query head
+    // within the group, and that row's addresses in Q, dO and the row data
+    // (lse2 of a head, then -D).  Advanced by additions only.
+    const int64_t qsh = 2 * a.q_sh, dsh = 2 * a.do_sh, rsh = 8 * (int64_t)a.L;
+    const int64_t qwrap = a.G * qsh + 32 * qst, dwrap = a.G * dsh + 32 * dst, rwrap = a.G * rsh + 128;
+    int ni = grp, nh = grp % a.G, nr0 = a.L - 32 * (grp / a.G + 1);
+    const char *nq = (const char *)(a.q + b * a.q_sb) + (kvh * a.G + nh) * qsh + nr0 * qst;
+    const char *nd = (const char *)(a.dout + b * a.do_sb) + (kvh * a.G + nh) * dsh + nr0 * dst;
+    const char *nr = (const char *)a.dl + ((int64_t)b * a.Hq + kvh * a.G + nh) * rsh + 4 * (int64_t)nr0;
+    auto advance = [&]() {
+        ni += 2;
+        nh += 2;
+        nq += 2 * qsh;
+        nd += 2 * dsh;
+        nr += 2 * rsh;
+        while (nh >= a.G) {
+            nh -= a.G;
+            nr0 -= 32;
+            nq -= qwrap;
+            nd -= dwrap;
+            nr -= rwrap;
         }
     };
-    auto store_rowinfo = [&](int it) {
-        if (gtid < 32) {
-            const int st = it >> 1 & 1;
-            sdl[grp][st][0][gtid] = lreg;
-            sdl[grp][st][1][gtid] = dreg;
-            skend[grp][st][gtid] = kreg;
+    // Load part i (0 .. 2 NI) of the next chunk into stage st: the parts are
+    // issued between the MFMAs of the current chunk.  A chunk with rows
+    // before 0, or rows too far apart, is loaded whole in part 0 with
+    // per-lane addresses.
+    constexpr int NPART = 2 * NI + 1;
+    auto issue_part = [&](int i, int st) {
+        if (ni >= total) return;
+        const uint32_t base = lds_addr(smem) + (uint32_t)(2 * TILEK + (grp * 2 + st) * 2 * TILEC);
+        const uint32_t rl = lds_addr((const char *)&srow[grp][st][0]);
+        if (nr0 < 0 || wide) {
+            if (i) return;
+            // (the lane is hidden from the optimiser, so that what this rare
+            // path derives from it is not hoisted and held in registers)
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            dma_rows<D, 4, 32>(nq - nr0 * qst, qst, nr0, a.L - 1, base, sub, ln);
+            dma_rows<D, 4, 32>(nd - nr0 * dst, dst, nr0, a.L - 1, base + TILEC, sub, ln);
+            const int64_t r = max(nr0 + (ln & 31), 0);
+            if (sub == 0) dma4(nr + 4 * (r - nr0 + (ln >> 5) * (int64_t)a.L), rl);
+            if (sub == 1) dma4(kend_b + r, rl + 256);
+        } else if (i < NI) {
+            dma16s(nq + i * (4 * RPW) * qst, qofs, base + i * 4096 + sub * 1024);
+        } else if (i < 2 * NI) {
+            dma16s(nd + (i - NI) * (4 * RPW) * dst, dofs, base + TILEC + (i - NI) * 4096 + sub * 1024);
+        } else {
+            if (sub == 0) dma4s(nr, rofs, rl);
+            if (sub == 1) dma4s((const char *)(kend_b + nr0), eofs, rl + 256);
         }
     };
+    // LDS read addresses: Q / dO fragments (row l32, chunk 2 kk + hf) relative
+    // to this group's stage 0, K / V fragments of this wave's keys, and the
+    // transpose reads of dO / Q
     const uint32_t kbase = (uint32_t)(l32 * ROWB + 16 * (hf ^ swz<D>(l32)));
     uint32_t tb[2];
     tr_bases<D>(lane, tb);
+    const char *ctile = smem + 2 * TILEK + grp * 4 * TILEC;
+    const char *ktile = smem + 32 * sub * ROWB, *vtile = ktile + TILEK;
 
     f32x16 dk[MD], dv[MD];
 #pragma unroll
     for (int md = 0; md < MD; ++md)
 #pragma unroll
         for (int v = 0; v < 16; ++v) dk[md][v] = dv[md][v] = 0.f;
-    if (grp < total) {
-        issue_chunk(grp);
-        store_rowinfo(grp);
+    // One chunk of 32 query rows (from row r0) in stage st
+    auto chunk = [&](int st, int r0) {
+        const char *qt = ctile + st * 2 * TILEC, *dt = qt + TILEC;
+        const float *ri = &srow[grp][st][4 * hf];
+        // One MFMA stream in which every vector instruction stands beside a
+        // matrix instruction that does not need it: S = Q K^T; then
+        // dP - D = dO V^T - D (accumulated from -D) beside P = exp2(S c2 -
+        // lse2); then dV^T += dO^T P beside dS = P (dP - D); then dK^T +=
+        // Q^T dS.  Operands are read AH steps ahead; the fences keep this
+        // order.
+        f32x16 S, dP;
+        f32x4 l4[4];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) S[v] = 0.f;
+        bf16x8 fa[AH + 1], fb[AH + 1];
+        auto rd = [&](int i) {
+            const char *ct = i < KK ? qt : dt, *ot = i < KK ? ktile : vtile;
+            const uint32_t x = kbase ^ (uint32_t)(32 * (i % KK));
+            fa[i % (AH + 1)] = *(const bf16x8 *)(ct + x);
+            fb[i % (AH + 1)] = *(const bf16x8 *)(ot + x);
+        };
+#pragma unroll
+        for (int i = 0; i < AH; ++i) rd(i);
+#pragma unroll
+        for (int i = 0; i < 2 * KK; ++i) {
+            if (i + AH < 2 * KK) rd(i + AH);
+            if (i >= KK - 4 && i < KK) {
+                const int gq = i - (KK - 4);
+                l4[gq] = *(const f32x4 *)(ri + 8 * gq);
+                const f32x4 d4 = *(const f32x4 *)(ri + 32 + 8 * gq);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dP[4 * gq + e] = d4[e];
+            }
+            if (i < KK) {
+                S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i % (AH + 1)], fb[i % (AH + 1)], S, 0, 0, 0);
+            } else {
+                dP = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i % (AH + 1)], fb[i % (AH + 1)], dP, 0, 0, 0);
+                constexpr int PS = 16 / KK;
+#pragma unroll
+                for (int u = 0; u < PS; ++u) {
+                    const int v = PS * (i - KK) + u;
+                    S[v] = fast_exp2(__builtin_fmaf(S[v], c2, -l4[v >> 2][v & 3]));
+                }
+            }
+            if (i >= 1 && i <= NPART) issue_part(i - 1, st ^ 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (r0 < im) {
+            // (a real branch: the compiler would otherwise turn this rare
+            // path into selects executed on every chunk)
+            int ln = lane;
+            asm volatile("" : "+v"(ln) :: "memory");
+            const int ky = kw0 + 32 * sub + (ln & 31);
+#pragma unroll
+            for (int gq = 0; gq < 4; ++gq) {
+                const int r = 8 * gq + 4 * (ln >> 5);
+                const i32x4 ke = *(const i32x4 *)&srow[grp][st][64 + r];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    S[4 * gq + e] = (r0 + r + e >= 0) & (ky < ke[e]) ? S[4 * gq + e] : 0.f;
+            }
+        }
+        // P (rows 8 (v / 4) + 4 hf + v % 4 of the lane's key) as B fragments
+        bf16x8 pf[2], dsf[2], fr[AH + 1];
+#pragma unroll
+        for (int i = 0; i < AH; ++i) fr[i] = tr_frag<D>(dt, tb, i / MD, i % MD);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) pf[v >> 3][v & 7] = (__bf16)S[v];
+#pragma unroll
+        for (int i = 0; i < 4 * MD; ++i) {
+            const int n = i + AH;
+            if (n < 4 * MD) fr[n % (AH + 1)] = tr_frag<D>(n < 2 * MD ? dt : qt, tb, n / MD % 2, n % MD);
+            const int ks = i / MD % 2, md = i % MD;
+            if (i < 2 * MD) {
+                dv[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % (AH + 1)], pf[ks], dv[md], 0, 0, 0);
+                constexpr int PS = 8 / MD;
+#pragma unroll
+                for (int u = 0; u < PS; ++u) {
+                    const int v = PS * i + u;
+                    dsf[v >> 3][v & 7] = (__bf16)(S[v] * dP[v]);
+                }
+            } else {
+                dk[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % (AH + 1)], dsf[ks], dk[md], 0, 0, 0);
+            }
+            if (i == 2 * MD) advance();   // (the loads of the current next chunk are all issued)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    const bool any = grp < total;
+    int r0 = nr0;   // first row of the current step's chunk
+    if (any) {
+#pragma unroll
+        for (int i = 0; i < NPART; ++i) issue_part(i, 0);
+        advance();
     }
     wait_vm_lgkm<0>();
     wg_barrier();
-    const char *ktile = smem + 32 * sub * ROWB, *vtile = smem + TILEK + 32 * sub * ROWB;
     for (int s = 0; s < nstep; ++s) {
-        const int it = 2 * s + grp;          // this group's chunk
-        const int nx = it + 2;               // its next one (other stage)
-        if (nx < total) issue_chunk(nx);
-        if (it < total) {
-            const int st = it >> 1 & 1;
-            const char *qt = smem + chunk_base(it), *dt = qt + TILEC;
-            // S = Q K^T and dP = dO V^T: query rows x this wave's 32 keys
-            f32x16 S, dP;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) S[v] = dP[v] = 0.f;
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) {
-                const bf16x8 qa = *(const bf16x8 *)(qt + (kbase ^ (32 * kk)));
-                const bf16x8 kb = *(const bf16x8 *)(ktile + (kbase ^ (32 * kk)));
-                S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kb, S, 0, 0, 0);
-                const bf16x8 da = *(const bf16x8 *)(dt + (kbase ^ (32 * kk)));
-                const bf16x8 vb = *(const bf16x8 *)(vtile + (kbase ^ (32 * kk)));
-                dP = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da, vb, dP, 0, 0, 0);
-            }
-            // the lane's 16 query rows 8 (v / 4) + 4 hf + v % 4
-            bf16x8 pf[2], dsf[2];
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                const f32x4 l4 = *(const f32x4 *)&sdl[grp][st][0][8 * gq + 4 * hf];
-                const f32x4 d4 = *(const f32x4 *)&sdl[grp][st][1][8 * gq + 4 * hf];
-                const int4 k4 = *(const int4 *)&skend[grp][st][8 * gq + 4 * hf];
-                const int ke[4] = {k4.x, k4.y, k4.z, k4.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int v = 4 * gq + e;
-                    const float p0 = fast_exp2(__builtin_fmaf(S[v], c2, -l4[e]));
-                    const float p = key < ke[e] ? p0 : 0.f;
-                    pf[v >> 3][v & 7] = (__bf16)p;
-                    dsf[v >> 3][v & 7] = (__bf16)(p * (dP[v] - d4[e]));
-                }
-            }
-            // dV^T += dO^T P and dK^T += Q^T dS
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-                for (int md = 0; md < MD; ++md) {
-                    dv[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag<D>(dt, tb, ks, md), pf[ks], dv[md], 0, 0, 0);
-                    dk[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag<D>(qt, tb, ks, md), dsf[ks], dk[md], 0, 0, 0);
-                }
-        }
-        // the row data of the next chunk goes to the other stage, which was
-        // last read before the previous barrier
-        if (nx < total) store_rowinfo(nx);
+        // (a group without a chunk in the last step has nothing left to load)
+        const int rn = nr0;
+        if (2 * s + grp < total) chunk(s & 1, r0);
+        r0 = rn;
         wait_vm_lgkm<0>();   // the next chunks landed; this step's LDS reads are done
         wg_barrier();
     }

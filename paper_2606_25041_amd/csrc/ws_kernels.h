@@ -142,11 +142,14 @@ struct BwdArgs {
     int64_t dq_sb, dq_st, dq_sh;
     int64_t dk_sb, dk_st, dk_sh;
     int64_t dv_sb, dv_st, dv_sh;
-    // workspace: per row (lse * log2(e), rowsum(dO * O)) [B][Hq][L], and the
-    // end of the keys each token sees [B][L]
+    // workspace: per row lse * log2(e) and -rowsum(dO * O), [B][Hq][2][L],
+    // and the end of the keys each token sees [B][L]
     float *dl;
     int32_t *kend;
     int32_t B, L, Hq, Hkv, G;
+    // a token stride of q, k, v or dout is too long for the 32-bit row
+    // offsets of a tile
+    int32_t wide_strides;
     float scale, scale_log2;
 };
 

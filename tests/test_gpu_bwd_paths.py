@@ -1,0 +1,64 @@
+"""GPU gradients at the edges of the kernels' load and mask paths: sequence
+lengths around a 32-row chunk and a 128-key tile, and token strides too long
+for the 32-bit row offsets of a tile (per-lane addresses instead)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2606_25041_amd as ws
+from paper_2606_25041_amd import inputs
+from tests import gpu_support as gs
+
+pytestmark = pytest.mark.gpu
+
+# rounding of P and dS to bf16 and of D's bf16 output, as in test_gpu_bwd
+MAX_ABS, MEAN_ABS = 2e-2, 2e-3
+
+
+def _case(B, Hq, Hkv, D, lens, seed, text=None):
+    wl = inputs.prefill_workload("bwd_paths", B, Hq, Hkv, D, lens, seed)
+    wl.text_starts = text
+    dout = inputs.bf16_normal(inputs.rng(seed, 9), wl.q.shape)
+    q, k, v = (gs.to_dev_bf16(t) for t in (wl.q, wl.k, wl.v))
+    o, lse = ws.block_causal_prefill(q, k, v, wl.offsets, want_lse=True, text_starts=text)
+    return wl, q, k, v, o, gs.to_dev_bf16(dout), lse, dout
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("L", [1, 31, 32, 33, 127, 129, 160, 257])
+def test_bwd_chunk_and_tile_edges(D, L):
+    rng = np.random.default_rng(L)
+    cuts = np.sort(rng.integers(0, L + 1, size=3))
+    lens = np.diff(np.concatenate([[0], cuts, [L]]))
+    text = (np.cumsum(lens) - np.minimum(lens, 2)).astype(np.int32)[None]
+    gs.say(f"[gpu] bwd edges D={D} L={L} blocks={lens.tolist()}")
+    wl, q, k, v, o, d, lse, dout = _case(1, 6, 2, D, [lens], 900 + L + D, text)
+    got = ws.block_causal_prefill_bwd(q, k, v, o, d, lse, wl.offsets, text_starts=text)
+    ref = oracle.prefill_bwd(inputs.bf16_bits(wl.q), inputs.bf16_bits(wl.k), inputs.bf16_bits(wl.v),
+                             inputs.bf16_bits(dout), wl.offsets, wl.scale, text_starts=text)
+    for name, x, r in zip(("dq", "dk", "dv"), got, ref):
+        err = np.abs(x.double().cpu().numpy() - r)
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (name, err.max(), err.mean())
+
+
+def test_bwd_token_stride_beyond_32_bit_offsets():
+    """Rows 2^24 elements apart give bitwise the packed tensors' gradients."""
+    L, H, D, st = 45, 2, 64, 1 << 24
+    gs.say("[gpu] bwd long token strides")
+    wl, q, k, v, o, d, lse, _ = _case(1, H, H, D, [np.array([20, 25])], 977)
+    ref = ws.block_causal_prefill_bwd(q, k, v, o, d, lse, wl.offsets)
+
+    def spread(t):
+        buf = torch.empty((L - 1) * st + H * D, dtype=torch.bfloat16, device="cuda")
+        far = buf.as_strided((1, L, H, D), (0, st, D, 1))
+        far.copy_(t)
+        return far
+
+    for which in range(4):
+        args = [q, k, v, d]
+        args[which] = spread(args[which])
+        got = ws.block_causal_prefill_bwd(args[0], args[1], args[2], o, args[3], lse, wl.offsets)
+        for x, r in zip(got, ref):
+            assert torch.equal(x, r)
+        del args
