@@ -378,8 +378,13 @@ int ws_block_causal_prefill_text(ws_tensor4 q, ws_tensor4 k, ws_tensor4 v,
  *   dk, dv:     f32 [batch][seq_len][num_kv_heads][head_dim] (written)
  *   workspace:  device scratch of ws_workspace_bytes(WS_OP_PREFILL_BWD,
  *               batch, num_q_heads, num_kv_heads, seq_len, seq_len) bytes,
- *               16-byte aligned; contents on entry ignored
- * The gradients are deterministic (fixed summation order; no atomics).
+ *               16-byte aligned; contents on entry ignored.  Part of it
+ *               holds partial sums on shapes whose dK/dV work is split to
+ *               fill the chip; 8 * batch * num_q_heads * seq_len bytes
+ *               (rounded up to 256) + 4 * batch * seq_len are enough to run,
+ *               unsplit
+ * The gradients are deterministic (fixed summation order for a given shape,
+ * device and size of workspace; no atomics).
  * Errors: WS_ERR_NULL, WS_ERR_SHAPE, WS_ERR_UNSUPPORTED, WS_ERR_ALIGN,
  * WS_ERR_HEADS, WS_ERR_OFFSETS, WS_ERR_WORKSPACE, WS_ERR_HIP.
  */

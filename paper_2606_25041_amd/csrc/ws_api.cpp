@@ -215,8 +215,96 @@ ws::TileShape plan_prefill(int) { return default_shape(); }
 size_t bwd_dl_bytes(int batch, int hq, int seq) {
     return ((size_t)batch * hq * seq * 2 * sizeof(float) + 255) / 256 * 256;
 }
-size_t bwd_workspace(int batch, int hq, int seq) {
+size_t bwd_rows_bytes(int batch, int hq, int seq) {
     return bwd_dl_bytes(batch, hq, seq) + (size_t)batch * seq * sizeof(int32_t);
+}
+
+// dK/dV work-groups: by default one per (stream, KV head, 128 keys), which
+// walks every 32-row chunk that sees those keys; the first keys are seen by
+// every row, so on a short sequence, or with few KV heads, the longest
+// work-groups set the time while most compute units idle (2.4k tokens, 8 KV
+// heads: 160 work-groups, the longest 3x the mean load of a unit).  A key
+// tile of more than a given number of chunks is then split: s0 parts for the
+// longest tile, fewer for the others.  The count is the smallest within 3 %
+// of the least modelled time, in steps of two chunks (~1.6 us): the longest
+// work-group, or the mean load of a unit plus 0.3 of the longest (their
+// uneven last round; against a simulated longest-first dispatch over 150
+// shapes this picks within 3 % of the best count on average), plus what the
+// partial sums cost (4 steps to write, about as much to read back, and 3 for
+// the second launch).  A split has to win 15 %: it gives up the unsplit
+// order, whose key tiles share rows in an XCD's L2 (8.3k tokens, 8 KV heads,
+// modelled gain 5 %: 2.06 ms split, 1.99 ms unsplit; 4.2k tokens, modelled
+// gain 40 %: 0.57 against 0.63).  split_tiles = 0: no split.
+struct BwdPlan {
+    int split_tiles = 0;
+    uint16_t tile_start[ws::BWD_MAX_SPLIT_TILES + 1];
+};
+
+// first_row[kt]: the first row that sees key 128 kt (never decreasing; NULL:
+// as if every block held one token).  max_parts: room for partial sums.
+BwdPlan plan_bwd(int num_cus, int batch, int hq, int hkv, int seq, const int32_t *first_row, int64_t max_parts) {
+    BwdPlan p;
+    const int64_t nkt = ((int64_t)seq + 127) / 128, ngrp = (int64_t)batch * hkv, G = hq / hkv;
+    if (nkt > ws::BWD_MAX_SPLIT_TILES || num_cus <= 0) return p;
+    constexpr double FIXED = 5, PART = 4, SUM = 3;   // steps per work-group, per part, of the second launch
+    int64_t chunks[ws::BWD_MAX_SPLIT_TILES];
+    for (int64_t kt = 0; kt < nkt; ++kt)
+        chunks[kt] = G * ((seq - (first_row ? first_row[kt] : 128 * kt) + 31) / 32);
+    auto parts = [&](int64_t kt, int64_t most) -> int64_t { return (chunks[kt] + most - 1) / most; };
+    auto share = [&](int s0) -> int64_t { return (chunks[0] + s0 - 1) / s0; };
+    double base = 0, lo = 0, cost[ws::BWD_MAX_SPLITS + 1];
+    int tried = 0;
+    for (int s0 = 1; s0 <= ws::BWD_MAX_SPLITS; ++s0) {
+        const int64_t most = share(s0);
+        double sum = 0, longest = 0;
+        int64_t n = 0, np = 0;
+        for (int64_t kt = 0; kt < nkt; ++kt) {
+            const int64_t k = parts(kt, most);
+            const double one = chunks[kt] / 2.0 / k + FIXED + (k > 1 ? PART : 0);
+            sum += k * one;
+            longest = std::max(longest, one);
+            n += k;
+            if (k > 1) np += k;
+        }
+        if (np > max_parts) break;
+        cost[s0] = std::max(longest, sum * ngrp / num_cus + (n * ngrp > num_cus ? 0.3 * longest : 0));
+        if (np) cost[s0] += SUM + PART * np * ngrp / num_cus;
+        if (s0 == 1) base = lo = cost[1];
+        lo = std::min(lo, cost[s0]);
+        tried = s0;
+        // no split brings the time below the mean load; past four rounds of
+        // work-groups more parts only add cost
+        if ((s0 == 1 && base <= 1.15 * sum * ngrp / num_cus) || n * ngrp > 4 * num_cus) break;
+    }
+    if (tried <= 1 || base <= 1.15 * lo) return p;
+    int s0 = 2;
+    while (cost[s0] > 1.03 * lo) ++s0;
+    int64_t at = 0;
+    for (int64_t kt = 0; kt < nkt; ++kt) {
+        const int64_t k = parts(kt, share(s0));
+        p.tile_start[kt] = (uint16_t)at;
+        at += k;
+        if (k > 1) p.split_tiles = (int)kt + 1;
+    }
+    p.tile_start[nkt] = (uint16_t)at;
+    return p;
+}
+
+size_t bwd_part_offset(int batch, int hq, int seq) { return (bwd_rows_bytes(batch, hq, seq) + 255) / 256 * 256; }
+
+// bytes of the partial sums of one part: 2 x 128 keys x D floats per group
+// (the largest head dim, which the size query does not know)
+size_t bwd_part_bytes(int batch, int hkv) { return (size_t)batch * hkv * 2 * 128 * WS_MAX_HEAD_DIM * sizeof(float); }
+
+// The row data, then room for the parts that a sequence of short blocks
+// would be split into (the largest case is the plan's own choice: with longer
+// blocks it takes what fits).
+size_t bwd_workspace(int batch, int hq, int hkv, int seq) {
+    int cus = 0;
+    if (ws::current_device_cus(&cus)) cus = 0;   // no device: the row data only
+    const BwdPlan p = plan_bwd(cus, batch, hq, hkv, seq, nullptr, INT32_MAX);
+    if (!p.split_tiles) return bwd_rows_bytes(batch, hq, seq);
+    return bwd_part_offset(batch, hq, seq) + p.tile_start[p.split_tiles] * bwd_part_bytes(batch, hkv);
 }
 
 // Total work items; fails when the grid would not fit the kernel's int math.
@@ -284,7 +372,7 @@ size_t ws_workspace_bytes(int32_t op, int32_t batch, int32_t num_q_heads, int32_
     if (op == WS_OP_PREFILL_BWD) {
         if (batch <= 0 || num_q_heads <= 0 || num_kv_heads <= 0 || num_q_heads % num_kv_heads || max_q <= 0)
             return 0;
-        return bwd_workspace(batch, num_q_heads, max_q);
+        return bwd_workspace(batch, num_q_heads, num_kv_heads, max_q);
     }
     if (op != WS_OP_STEP) return 0;
     if (batch <= 0 || num_q_heads <= 0 || num_kv_heads <= 0 || num_q_heads % num_kv_heads || max_q <= 0 ||
@@ -473,7 +561,7 @@ int ws_block_causal_prefill_bwd(ws_tensor4 q, ws_tensor4 k, ws_tensor4 v, ws_ten
     }
     const int64_t work = (int64_t)batch * num_q_heads * ((seq_len + 127) / 128);
     if (work > INT32_MAX) return fail(WS_ERR_SHAPE, "too many work items");
-    const size_t need = bwd_workspace(batch, num_q_heads, seq_len);
+    const size_t need = bwd_rows_bytes(batch, num_q_heads, seq_len);
     if (!workspace || workspace_bytes < need || !aligned16(workspace))
         return fail(WS_ERR_WORKSPACE, "workspace needs %zu bytes (16-byte aligned), got %zu", need,
                     workspace ? workspace_bytes : (size_t)0);
@@ -497,6 +585,32 @@ int ws_block_causal_prefill_bwd(ws_tensor4 q, ws_tensor4 k, ws_tensor4 v, ws_ten
     a.B = batch; a.L = seq_len; a.Hq = num_q_heads; a.Hkv = num_kv_heads; a.G = num_q_heads / num_kv_heads;
     a.scale = scale;
     a.scale_log2 = scale * 1.4426950408889634f;
+    // the split needs room for its partial sums; a workspace that only holds
+    // the row data runs without
+    const size_t part_at = bwd_part_offset(batch, num_q_heads, seq_len), part_bytes = bwd_part_bytes(batch, num_kv_heads);
+    if (workspace_bytes >= part_at + 2 * part_bytes && seq_len <= 128 * ws::BWD_MAX_SPLIT_TILES) {
+        // the first row of any stream that sees each tile's first key
+        int32_t first_row[ws::BWD_MAX_SPLIT_TILES];
+        for (int kt = 0; kt < (seq_len + 127) / 128; ++kt) first_row[kt] = 128 * kt;
+        for (int b = 0; b < batch; ++b) {
+            const int32_t *off = block_offsets_host + (int64_t)b * (num_blocks + 1);
+            int n = 0;
+            for (int kt = 0; kt < (seq_len + 127) / 128; ++kt) {
+                const int32_t key = 128 * kt;
+                while (off[n + 1] <= key) ++n;
+                // a key of a token-causal segment is seen from its own row on
+                if (!text_starts_host || key < text_starts_host[(int64_t)b * num_blocks + n])
+                    first_row[kt] = std::min(first_row[kt], off[n]);
+            }
+        }
+        int cus = 0;
+        if (ws::current_device_cus(&cus)) cus = 0;
+        const BwdPlan p = plan_bwd(cus, batch, num_q_heads, num_kv_heads, seq_len, first_row,
+                                   (int64_t)((workspace_bytes - part_at) / part_bytes));
+        a.split_tiles = p.split_tiles;
+        if (p.split_tiles) std::memcpy(a.tile_start, p.tile_start, sizeof a.tile_start);
+        a.part = (float *)((char *)workspace + part_at);
+    }
     if (int e = ws::launch_prefill_bwd(a, head_dim, stream))
         return fail(WS_ERR_HIP, "backward launch failed (hip error %d)", e);
     return ok();

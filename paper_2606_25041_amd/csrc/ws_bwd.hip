@@ -336,8 +336,21 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(const BwdArgs a) {
     // (one L2 read serves them); the launch is rounded up to whole blocks
     // and work-groups past the last key tile exit at once.
     const int ngrp = a.B * a.Hkv;
-    int kt, grpi;
-    if (ngrp % NUM_XCD == 0) {
+    int kt, grpi, split = 0, nsplit = 1;
+    if (a.split_tiles) {
+        // items in tile order, the groups as the fast digit (with a multiple
+        // of 8 groups each stays on one XCD)
+        const int it = wid / ngrp;
+        grpi = wid - it * ngrp;
+        int lo = 0, hi = nkt - 1;   // the last tile that starts at or before it
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (a.tile_start[mid] <= it) lo = mid; else hi = mid - 1;
+        }
+        kt = lo;
+        split = it - a.tile_start[kt];
+        nsplit = a.tile_start[kt + 1] - a.tile_start[kt];
+    } else if (ngrp % NUM_XCD == 0) {
         const int gpx = ngrp / NUM_XCD, x = wid % NUM_XCD, l = wid / NUM_XCD;
         const int kb = l / (gpx * KB_DKDV), r = l - kb * gpx * KB_DKDV;
         const int gi = r / KB_DKDV;
@@ -383,9 +396,12 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(const BwdArgs a) {
     // (different key tiles, running side by side) then read the same rows at
     // about the same time and the L2 serves them once.  Rows before i0 see
     // none of these keys, so the masking zeroes their terms.
+    // A split takes a contiguous share [first, total) of the chunks; group grp
+    // takes chunks first + grp, first + grp + 2, ...
     const int nch = (a.L - i0 + 31) / 32;
-    const int total = a.G * nch;            // chunks; group grp takes chunks grp, grp + 2, ...
-    const int nstep = (total + 1) / 2;
+    const int first = (int)((int64_t)a.G * nch * split / nsplit);
+    const int total = (int)((int64_t)a.G * nch * (split + 1) / nsplit);
+    const int nstep = (total - first + 1) / 2;
 
     // Rows from im on see every key of this wave, so a chunk whose first row
     // is at or past im needs no element masks (key ends do not decrease).
@@ -412,13 +428,13 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(const BwdArgs a) {
     // lanes 0..31 fetch lse2 and lanes 32..63 -D of the chunk's rows
     const uint32_t rofs = 4u * (uint32_t)(l32 + hf * a.L), eofs = 4u * (uint32_t)l32;
     const bool wide = a.wide_strides != 0;   // 32-bit row offsets do not reach
-    // Next chunk to load (this group's chunks are grp, grp + 2, ...): its
+    // Next chunk to load (chunk ni of the tile): its
     // first row (may be negative: rows before 0 are no rows), its query head
     // within the group, and that row's addresses in Q, dO and the row data
     // (lse2 of a head, then -D).  Advanced by additions only.
     const int64_t qsh = 2 * a.q_sh, dsh = 2 * a.do_sh, rsh = 8 * (int64_t)a.L;
     const int64_t qwrap = a.G * qsh + 32 * qst, dwrap = a.G * dsh + 32 * dst, rwrap = a.G * rsh + 128;
-    int ni = grp, nh = grp % a.G, nr0 = a.L - 32 * (grp / a.G + 1);
+    int ni = first + grp, nh = ni % a.G, nr0 = a.L - 32 * (ni / a.G + 1);
     const char *nq = (const char *)(a.q + b * a.q_sb) + (kvh * a.G + nh) * qsh + nr0 * qst;
     const char *nd = (const char *)(a.dout + b * a.do_sb) + (kvh * a.G + nh) * dsh + nr0 * dst;
     const char *nr = (const char *)a.dl + ((int64_t)b * a.Hq + kvh * a.G + nh) * rsh + 4 * (int64_t)nr0;
@@ -538,7 +554,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(const BwdArgs a) {
                 const i32x4 ke = *(const i32x4 *)&srow[grp][st][64 + r];
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    S[4 * gq + e] = (r0 + r + e >= 0) & (ky < ke[e]) ? S[4 * gq + e] : 0.f;
+                    S[4 * gq + e] = ((r0 + r + e >= 0) & (ky < ke[e])) ? S[4 * gq + e] : 0.f;
             }
         }
         // P (rows 8 (v / 4) + 4 hf + v % 4 of the lane's key) as B fragments
@@ -567,7 +583,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(const BwdArgs a) {
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    const bool any = grp < total;
+    const bool any = first + grp < total;
     int r0 = nr0;   // first row of the current step's chunk
     if (any) {
 #pragma unroll
@@ -579,7 +595,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(const BwdArgs a) {
     for (int s = 0; s < nstep; ++s) {
         // (a group without a chunk in the last step has nothing left to load)
         const int rn = nr0;
-        if (2 * s + grp < total) chunk(s & 1, r0);
+        if (first + 2 * s + grp < total) chunk(s & 1, r0);
         r0 = rn;
         wait_vm_lgkm<0>();   // the next chunks landed; this step's LDS reads are done
         wg_barrier();
@@ -598,6 +614,25 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(const BwdArgs a) {
     }
     wait_vm_lgkm<0>();
     wg_barrier();
+    if (grp == 0 && nsplit > 1) {
+        // this split's sums, unscaled, in register order (1 KB per store)
+        float *pp = a.part + (((int64_t)(a.tile_start[kt] + split) * ngrp + grpi) * 2 * 128 + 32 * sub) * D + 4 * lane;
+#pragma unroll
+        for (int md = 0; md < MD; ++md)
+#pragma unroll
+            for (int gq = 0; gq < 4; ++gq) {
+                f32x4 kv, vv;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int v = 4 * gq + e;
+                    kv[e] = dk[md][v] + part[pbase + (md * 16 + v) * 64];
+                    vv[e] = dv[md][v] + part[4 * MD * 16 * 64 + pbase + (md * 16 + v) * 64];
+                }
+                *(f32x4 *)(pp + (md * 4 + gq) * 256) = kv;
+                *(f32x4 *)(pp + 128 * D + (md * 4 + gq) * 256) = vv;
+            }
+        return;
+    }
     if (grp == 0 && key < a.L) {
         float *kp = a.dk + b * a.dk_sb + (int64_t)key * a.dk_st + kvh * a.dk_sh;
         float *vp = a.dv + b * a.dv_sb + (int64_t)key * a.dv_st + kvh * a.dv_sh;
@@ -618,6 +653,42 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(const BwdArgs a) {
     }
 }
 
+// Adds the partial sums of the split key tiles in split order and writes dK
+// and dV.  One thread per 4 elements (one register group of one lane of the
+// kernel above); bound by reading the partials.
+template <int D>
+__global__ __launch_bounds__(256) void bwd_sum_kernel(const BwdArgs a) {
+    constexpr int PER = 128 * D / 4 / 256;   // blocks per (tile, group, dK or dV)
+    const int ngrp = a.B * a.Hkv;
+    const int blk = blockIdx.x % PER, wh = blockIdx.x / PER % 2, tg = blockIdx.x / (2 * PER);
+    const int kt = tg / ngrp, grpi = tg - kt * ngrp;
+    const int s0 = a.tile_start[kt], ns = a.tile_start[kt + 1] - s0;
+    const int u = blk * 256 + threadIdx.x;   // ((sub * MD + md) * 4 + gq) * 64 + lane
+    const int64_t stride = (int64_t)ngrp * 2 * 128 * D;
+    const float *pp = a.part + (((int64_t)s0 * ngrp + grpi) * 2 + wh) * 128 * D + 4 * u;
+    f32x4 x[BWD_MAX_SPLITS];
+#pragma unroll
+    for (int s = 0; s < BWD_MAX_SPLITS; ++s)
+        if (s < ns) x[s] = *(const f32x4 *)(pp + s * stride);
+    f32x4 sum = x[0];
+#pragma unroll
+    for (int s = 1; s < BWD_MAX_SPLITS; ++s)
+        if (s < ns)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += x[s][e];
+    const int lane = u & 63, gq = (u >> 6) & 3, md = (u >> 8) % (D / 32), sub = (u >> 8) / (D / 32);
+    const int key = kt * 128 + 32 * sub + (lane & 31);
+    if (key >= a.L) return;
+    const int b = grpi / a.Hkv, kvh = grpi - b * a.Hkv;
+    const int d0 = 32 * md + 8 * gq + 4 * (lane >> 5);
+    float *op = wh ? a.dv + b * a.dv_sb + (int64_t)key * a.dv_st + kvh * a.dv_sh
+                   : a.dk + b * a.dk_sb + (int64_t)key * a.dk_st + kvh * a.dk_sh;
+    if (!wh)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] *= a.scale;
+    *(f32x4 *)(op + d0) = sum;
+}
+
 template <int D>
 int launch_bwd_t(const BwdArgs &a, hipStream_t st) {
     const int64_t rows = (int64_t)a.B * a.L * a.Hq;
@@ -628,6 +699,13 @@ int launch_bwd_t(const BwdArgs &a, hipStream_t st) {
     hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3((unsigned)(a.B * a.Hq * nqt)), dim3(256), 0, st, a);
     if (int e = (int)hipGetLastError()) return e;
     const int64_t ngrp = (int64_t)a.B * a.Hkv;
+    if (a.split_tiles) {
+        hipLaunchKernelGGL(bwd_dkdv_kernel<D>, dim3((unsigned)(ngrp * a.tile_start[nqt])), dim3(512), 0, st, a);
+        if (int e = (int)hipGetLastError()) return e;
+        constexpr int64_t PER = 128 * D / 4 / 256;
+        hipLaunchKernelGGL(bwd_sum_kernel<D>, dim3((unsigned)(a.split_tiles * ngrp * 2 * PER)), dim3(256), 0, st, a);
+        return (int)hipGetLastError();
+    }
     const int64_t grid = ngrp % NUM_XCD == 0 ? ngrp * ((nqt + KB_DKDV - 1) / KB_DKDV) * KB_DKDV : ngrp * nqt;
     hipLaunchKernelGGL(bwd_dkdv_kernel<D>, dim3((unsigned)grid), dim3(512), 0, st, a);
     return (int)hipGetLastError();

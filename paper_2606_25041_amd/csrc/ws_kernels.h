@@ -125,6 +125,11 @@ struct AppendArgs {
     int32_t B, Ln, Hkv, D;
 };
 
+// Key tiles (128 keys) of a dK/dV launch that may be split over work-groups,
+// and splits of one of them, at most.
+constexpr int BWD_MAX_SPLIT_TILES = 128;
+constexpr int BWD_MAX_SPLITS = 16;
+
 // Gradients of the whole-sequence path (contiguous K/V).  bf16 inputs,
 // f32 gradients; element strides.
 struct BwdArgs {
@@ -151,6 +156,15 @@ struct BwdArgs {
     // offsets of a tile
     int32_t wide_strides;
     float scale, scale_log2;
+    // dK/dV split over work-groups (split_tiles > 0): the work-groups of key
+    // tile kt are tile_start[kt] .. tile_start[kt + 1] - 1 (times the (stream,
+    // KV head) groups), each taking its share of the tile's row chunks.  The
+    // tiles with more than one, 0 .. split_tiles - 1, write f32 partial sums
+    // [tile_start[kt] + split][group][dK, dV][128 keys x D in register order],
+    // which a second launch adds up.
+    float *part;
+    int32_t split_tiles;
+    uint16_t tile_start[BWD_MAX_SPLIT_TILES + 1];
 };
 
 // Launch shapes compiled into the library.

@@ -62,3 +62,35 @@ def test_bwd_token_stride_beyond_32_bit_offsets():
         for x, r in zip(got, ref):
             assert torch.equal(x, r)
         del args
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,D,B", [
+    ([40] * 13, 8, 1, 128, 1),          # split shares that end inside a head's chunk run
+    ([700], 8, 2, 128, 1),              # one block: every key tile is seen by every row
+    ([33, 0, 1, 500, 211], 6, 2, 64, 2),
+    ([129], 32, 1, 64, 1),              # two tiles, the second of one key
+])
+def test_bwd_split_key_tiles(lens, Hq, Hkv, D, B):
+    """Shapes whose dK/dV work is split over work-groups (the size query asks
+    for more than the row data): against the oracle, and against the unsplit
+    sums, which a workspace of the row data alone selects.  The two differ in
+    the order of f32 sums only: at most (row chunks) x 2^-24 relative to the
+    sum of the terms' sizes; 1e-5 of the largest value is 3x the worst seen."""
+    lens = np.array(lens)
+    L = int(lens.sum())
+    gs.say(f"[gpu] bwd split {B}x{Hq}/{Hkv}x{D} L={L}")
+    text = np.tile((np.cumsum(lens) - np.minimum(lens, 5)).astype(np.int32), (B, 1))
+    wl, q, k, v, o, d, lse, dout = _case(B, Hq, Hkv, D, [lens] * B, 990 + L, text)
+    rows = (8 * B * Hq * L + 255) // 256 * 256 + 4 * B * L
+    assert ws.workspace_bytes(ws.WS_OP_PREFILL_BWD, B, Hq, Hkv, L, L) > rows
+    got = ws.block_causal_prefill_bwd(q, k, v, o, d, lse, wl.offsets, text_starts=text)
+    again = ws.block_causal_prefill_bwd(q, k, v, o, d, lse, wl.offsets, text_starts=text)
+    small = ws.block_causal_prefill_bwd(q, k, v, o, d, lse, wl.offsets, text_starts=text,
+                                        workspace=torch.empty(rows, dtype=torch.uint8, device="cuda"))
+    ref = oracle.prefill_bwd(inputs.bf16_bits(wl.q), inputs.bf16_bits(wl.k), inputs.bf16_bits(wl.v),
+                             inputs.bf16_bits(dout), wl.offsets, wl.scale, text_starts=text)
+    for name, x, y, z, r in zip(("dq", "dk", "dv"), got, again, small, ref):
+        assert torch.equal(x, y), name
+        assert (x - z).abs().max() <= 1e-5 * z.abs().max(), name
+        err = np.abs(x.double().cpu().numpy() - r)
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (name, err.max(), err.mean())
