@@ -1,7 +1,8 @@
 // gfx950 (MI355X) kernels for the gradients of whole-sequence block-causal
 // attention (training uses the same causal format as generation,
-// Wan-Streamer v0.1, Sec. 2.3): a per-row prep pass, a query-major dQ kernel
-// and a key-major dK/dV kernel, all deterministic.
+// Wan-Streamer v0.1, Sec. 2.3): a query-major dQ kernel, which also leaves
+// each row's D and key end for the key-major dK/dV kernel after it; both
+// deterministic.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -21,8 +22,10 @@ constexpr int AH = 2;         // LDS operand reads issued this many MFMAs ahead
 //   D_i = <dO_i, O_i>,  dS_ij = P_ij (<dO_i, v_j> - D_i),
 //   dQ_i = scale sum_j dS_ij k_j,  dK_j = scale sum_i dS_ij q_i,
 //   dV_j = sum_i P_ij dO_i.
-// Two kernels after a per-row prep pass: a query-major one for dQ (like the
-// forward, with dS^T in place of P^T) and a key-major one for dK and dV
+// Two kernels: a query-major one for dQ (like the forward, with dS^T in place
+// of P^T), which forms D_i from the rows of dO it holds anyway and stores it
+// (a pass of its own over O and dO took 10 us at 2.4k tokens, 119 us at
+// 2 x 16384), then a key-major one for dK and dV
 // (S = Q K^T with the keys as columns, so P and dS are B operands of
 // dV^T += dO^T P and dK^T += Q^T dS).  Each sums in a fixed order: the
 // gradients are deterministic, and dK/dV sum the G query heads of their KV
@@ -59,41 +62,6 @@ __device__ __forceinline__ void tr_bases(int lane, uint32_t (&tb)[2]) {
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-
-// Per row: lse * log2(e) and -<dO, O> (two rows of L per head), and, per
-// token, the end of the keys it sees.  LPR lanes per row, 16 bytes each.
-template <int D>
-__global__ __launch_bounds__(256) void bwd_prep_kernel(const BwdArgs a) {
-    constexpr int LPR = D / 8;
-    constexpr int RPB = 256 / LPR;
-    const int64_t nrows = (int64_t)a.B * a.L * a.Hq;
-    const int64_t r = (int64_t)blockIdx.x * RPB + threadIdx.x / LPR;
-    const int c = threadIdx.x % LPR;
-    float part = 0.f;
-    int h = 0, i = 0, b = 0;
-    if (r < nrows) {
-        h = (int)(r % a.Hq);
-        i = (int)((r / a.Hq) % a.L);
-        b = (int)(r / ((int64_t)a.Hq * a.L));
-        const u32x4 ov = *(const u32x4 *)(a.o + b * a.o_sb + (int64_t)i * a.o_st + h * a.o_sh + 8 * c);
-        const u32x4 dv = *(const u32x4 *)(a.dout + b * a.do_sb + (int64_t)i * a.do_st + h * a.do_sh + 8 * c);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) part += bf16_lo(ov[k]) * bf16_lo(dv[k]) + bf16_hi(ov[k]) * bf16_hi(dv[k]);
-    }
-#pragma unroll
-    for (int m = LPR / 2; m >= 1; m >>= 1) part += __shfl_xor(part, m, LPR);
-    if (r < nrows && c == 0) {
-        const int64_t idx = ((int64_t)b * a.Hq + h) * a.L + i;
-        float *dl = a.dl + 2 * ((int64_t)b * a.Hq + h) * a.L + i;
-        dl[0] = a.lse[idx] * 1.4426950408889634f;
-        dl[a.L] = -part;
-        if (h == 0) {
-            const int32_t *offs = a.offsets + (int64_t)b * (a.nb + 1);
-            const int32_t *text = a.text_starts ? a.text_starts + (int64_t)b * a.nb : nullptr;
-            a.kend[(int64_t)b * a.L + i] = row_key_end<false>(offs, text, a.nb, i);
-        }
-    }
-}
 
 // Loads rows [r0, r0 + nrows) of a [rows][D] bf16 tile (row r of the tile
 // = global row min(r0 + r, rmax), at least 0) straight into LDS at `lds` in the
@@ -149,24 +117,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int q0 = qt * 128;
     const int row = q0 + 32 * wave + l32;
     const int rc = min(row, a.L - 1);
-    const int32_t *kend_b = a.kend + (int64_t)b * a.L;
-    const int k_hi = ld_uniform(kend_b, min(q0 + 127, a.L - 1));
-    const int kfull = ld_uniform(kend_b, q0);
-    const int my_kend = kend_b[rc];
-    const float *dlr = a.dl + 2 * ((int64_t)b * a.Hq + h) * a.L + rc;
-    const float lse2 = dlr[0], nD = dlr[a.L];
+    const int32_t *offs = a.offsets + (int64_t)b * (a.nb + 1);
+    const int32_t *text = a.text_starts ? a.text_starts + (int64_t)b * a.nb : nullptr;
+    const int k_hi = row_key_end<true>(offs, text, a.nb, min(q0 + 127, a.L - 1));
+    const int kfull = row_key_end<true>(offs, text, a.nb, q0);
+    const int my_kend = row_key_end<false>(offs, text, a.nb, rc);
+    const float lse2 = a.lse[((int64_t)b * a.Hq + h) * a.L + rc] * 1.4426950408889634f;
     const float c2 = a.scale_log2;
 
-    // B fragments of the lane's query row: q and dO, head dims 16 kk + 8 hf + [0, 8)
+    // B fragments of the lane's query row: q and dO, head dims 16 kk + 8 hf +
+    // [0, 8), and -D = -<dO, O> from the row's output
     bf16x8 qf[KK], dof[KK];
+    float nD;
     {
         const uint16_t *qp = a.q + b * a.q_sb + (int64_t)rc * a.q_st + h * a.q_sh + 8 * hf;
         const uint16_t *dp = a.dout + b * a.do_sb + (int64_t)rc * a.do_st + h * a.do_sh + 8 * hf;
+        const uint16_t *op = a.o + b * a.o_sb + (int64_t)rc * a.o_st + h * a.o_sh + 8 * hf;
+        u32x4 ov[KK];
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
-            qf[kk] = *(const bf16x8 *)(qp + 16 * kk);
+            ov[kk] = *(const u32x4 *)(op + 16 * kk);
             dof[kk] = *(const bf16x8 *)(dp + 16 * kk);
+            qf[kk] = *(const bf16x8 *)(qp + 16 * kk);
         }
+        float part[KK];
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+            const u32x4 dv = __builtin_bit_cast(u32x4, dof[kk]);
+            part[kk] = 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                part[kk] += bf16_lo(ov[kk][k]) * bf16_lo(dv[k]) + bf16_hi(ov[kk][k]) * bf16_hi(dv[k]);
+        }
+#pragma unroll
+        for (int w = 1; w < KK; w *= 2)
+#pragma unroll
+            for (int kk = 0; kk < KK; kk += 2 * w) part[kk] += part[kk + w];
+        nD = -halves_sum(part[0]);
+    }
+    // the row data of the dK/dV launch: lse2 and -D of this head's row and,
+    // once per token, its key end
+    if (row < a.L && hf == 0) {
+        float *dl = a.dl + 2 * ((int64_t)b * a.Hq + h) * a.L + row;
+        dl[0] = lse2;
+        dl[a.L] = nD;
+        if (h == 0) a.kend[(int64_t)b * a.L + row] = my_kend;
     }
     const char *kg = (const char *)(a.k + b * a.k_sb + g * a.k_sh);
     const char *vg = (const char *)(a.v + b * a.v_sb + g * a.v_sh);
@@ -691,10 +686,6 @@ __global__ __launch_bounds__(256) void bwd_sum_kernel(const BwdArgs a) {
 
 template <int D>
 int launch_bwd_t(const BwdArgs &a, hipStream_t st) {
-    const int64_t rows = (int64_t)a.B * a.L * a.Hq;
-    const int64_t rpb = 256 / (D / 8);
-    hipLaunchKernelGGL(bwd_prep_kernel<D>, dim3((unsigned)((rows + rpb - 1) / rpb)), dim3(256), 0, st, a);
-    if (int e = (int)hipGetLastError()) return e;
     const int64_t nqt = (a.L + 127) / 128;
     hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3((unsigned)(a.B * a.Hq * nqt)), dim3(256), 0, st, a);
     if (int e = (int)hipGetLastError()) return e;

@@ -180,7 +180,7 @@ struct TileShape {
 int launch_attention(const AttnArgs &a, int head_dim, TileShape shape, void *stream);
 int launch_combine(const AttnArgs &a, int head_dim, void *stream);
 int launch_append(const AppendArgs &a, void *stream);
-// prep (row sums, key ends), then dQ and dK/dV; 0 or a HIP error code
+// dQ (with the row data), then dK/dV and the sum of its parts; 0 or a HIP error code
 int launch_prefill_bwd(const BwdArgs &a, int head_dim, void *stream);
 // Compute units of the current HIP device (queried once per device, then
 // cached): 0 and *cus set, or a HIP error code (e.g. no device).
