@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "../../include/ws_attn.h"
@@ -199,6 +200,149 @@ StepPlan plan_step(int num_cus, int batch, int hq, int hkv, int lq, int64_t max_
     if (const int s_ov = split_override()) ns = s_ov;
     p.nsplit = (int)ns;
     return p;
+}
+
+// Time, in tiles, of work-groups taken longest first by `cus` compute units:
+// groups of n equal items of `size` tiles, sizes not increasing.  Units with
+// the same load are kept together, so a round costs one entry.
+struct ItemGroup { int size, n; };
+int dispatch_time(int cus, const ItemGroup *groups, int ngroups) {
+    int total = 0;
+    for (int g = 0; g < ngroups; ++g) total += groups[g].n;
+    if (total <= cus) return groups[0].size;   // one round
+    constexpr int MAX = 64;
+    struct Load { int at, n; } q[MAX];   // ascending loads
+    int len = 1;
+    q[0] = {0, cus};
+    for (int g = 0; g < ngroups; ++g) {
+        int n = groups[g].n;
+        while (n > 0) {
+            const int k = std::min(n, q[0].n), to = q[0].at + groups[g].size;
+            n -= k;
+            if ((q[0].n -= k) == 0) std::move(q + 1, q + len--, q);
+            int i = len;
+            while (i > 0 && q[i - 1].at > to) --i;
+            if (i > 0 && q[i - 1].at == to) {
+                q[i - 1].n += k;
+            } else if (len < MAX) {
+                std::move_backward(q + i, q + len, q + len + 1);
+                q[i] = {to, k};
+                ++len;
+            } else {   // no room for another load: join the next higher one
+                q[i < len ? i : len - 1].n += k;
+            }
+        }
+    }
+    return q[len - 1].at;
+}
+
+// Splits of a step over streams whose key counts or block lengths differ.
+// One split count for all of them (plan_step) lets the longest stream set
+// the time: with caches of 32768, 9001, 2750 and 517 tokens and 8 KV heads,
+// 256 work-groups of which 64 run 64 tiles and the others 18 or fewer (mean
+// load 22; 77 us, with this plan 44).  Here a stream of n tiles gets ceil(n /
+// T) splits (or one split count after all, where that is better), chosen by
+// the least modelled time of the dispatch on one XCD's compute units; among
+// times within 2 % the fewest splits.  The streams' splits share the partial
+// slots of plan_step's plan (its split count x batch), so the workspace is
+// the same; a stream with one split writes its output itself and needs none.
+bool plan_ragged(ws::RaggedPlan &r, int num_cus, const StepPlan &uni, int batch, int hq, int hkv, int lq,
+                 const int32_t *cache_lens, const int32_t *nl, const int32_t *text) {
+    if (batch < 2 || batch > ws::LENS_IN_ARGS || split_override()) return false;
+    const int64_t qt = uni.shape.qtile(), G = hq / hkv;
+    struct Stream { int tiles, q, b; } st[ws::LENS_IN_ARGS];
+    bool differ = false;
+    for (int b = 0; b < batch; ++b) {
+        const int n = nl ? nl[b] : lq;
+        st[b] = {(int)(((int64_t)cache_lens[b] + n + 63) / 64), (int)((G * n + qt - 1) / qt), b};
+        differ = differ || st[b].tiles != st[0].tiles || st[b].q != st[0].q;
+    }
+    if (!differ) return false;
+    // longest first (few streams: insertion)
+    for (int i = 1; i < batch; ++i)
+        for (int j = i; j > 0 && st[j].tiles > st[j - 1].tiles; --j) std::swap(st[j], st[j - 1]);
+    // An XCD runs hkv * deal / 8 classes: its share of every stream's items is
+    // the stream's items x hkv / 8.
+    const int cus = std::max(1, num_cus * uni.shape.groups_per_cu() / ws::NUM_XCD);
+    const int64_t room = uni.nsplit > 1 ? (int64_t)uni.nsplit * batch : 0;
+    const int most = st[0].tiles;
+    int best_ns[ws::LENS_IN_ARGS], best = INT32_MAX, last = 0;
+    // Tries the longest stream in s splits and the others in pieces as long
+    // (s = 0: every stream in plan_step's count); false when more splits do
+    // not fit or no longer help.
+    auto attempt = [&](int s) -> bool {
+        const int T = s ? std::max((most + s - 1) / s, 2) : 0;
+        if (s && T == last) return true;
+        last = T;
+        int ns[ws::LENS_IN_ARGS];
+        ItemGroup grp[ws::LENS_IN_ARGS];
+        int64_t used = 0, items = 0;
+        for (int p = 0; p < batch; ++p) {
+            const int n = s ? std::min((st[p].tiles + T - 1) / T, WS_MAX_SPLITS)
+                            : std::min(uni.nsplit, std::max(1, st[p].tiles / 2));
+            const int64_t c = (int64_t)n * st[p].q * hkv;
+            ns[p] = n;
+            if (n > 1) used += n;
+            items += c;
+            ItemGroup x{(st[p].tiles + n - 1) / n + (int)SPLIT_FIXED_TILES,
+                        (int)std::min<int64_t>((c + ws::NUM_XCD - 1) / ws::NUM_XCD, INT32_MAX / ws::LENS_IN_ARGS)};
+            int i = p;
+            for (; i > 0 && grp[i - 1].size < x.size; --i) grp[i] = grp[i - 1];
+            grp[i] = x;
+        }
+        if (used > room) return false;
+        // (very many items: one split count's rounds are even enough)
+        const int64_t cap = 8 * (int64_t)cus * ws::NUM_XCD;
+        // the merge takes about as long as one tile per eight splits
+        const int merge = *std::max_element(ns, ns + batch) / 8;
+        const int t = items > 4 * cap ? INT32_MAX - 1 : dispatch_time(cus, grp, batch) + merge;
+        if (best == INT32_MAX || 50 * (int64_t)t < 49 * (int64_t)best) {
+            best = t;
+            std::copy(ns, ns + batch, best_ns);
+        }
+        return items <= cap;
+    };
+    // Lengths that hardly differ keep the common count, whose launch reads
+    // less: a 10 % gain is asked for, without splits a ratio of 5 / 4.
+    if (!room) {
+        if (5 * st[batch - 1].tiles * st[batch - 1].q >= 4 * st[0].tiles * st[0].q) return false;
+        attempt(1);
+    } else {
+        attempt(0);
+        const int uniform = best;
+        bool more = attempt(1);
+        for (int s = 2; more && s <= WS_MAX_SPLITS; ++s) more = attempt(s);
+        if (10 * (int64_t)best > 9 * (int64_t)uniform) return false;
+    }
+    int64_t at = 0, slot = 0;
+    r.max_nsplit = 1;
+    for (int p = 0; p < ws::LENS_IN_ARGS; ++p) {
+        ws::RaggedStream &x = r.pos[p];
+        x = {};
+        x.start = INT32_MAX;
+        if (p >= batch) continue;
+        const int b = st[p].b, n = best_ns[p];
+        x.start = (int32_t)at;
+        x.b = b;
+        x.ns = n;
+        x.slot = (int32_t)slot;
+        x.n_pool = cache_lens[b];
+        x.nl = nl ? nl[b] : lq;
+        x.text = text ? text[b] : lq;
+        x.items = st[p].q * n;
+        x.fd_ns = ws::fastdiv_make((uint32_t)n);
+        r.ns[b] = n;
+        r.slot[b] = (int32_t)slot;
+        r.max_nsplit = std::max(r.max_nsplit, n);
+        at += x.items;
+        if (n > 1) slot += n;
+    }
+    r.n_items = (int32_t)at;
+    r.deal = ws::NUM_XCD;
+    while (r.deal > 1 && hkv * (r.deal / 2) % ws::NUM_XCD == 0) r.deal /= 2;
+    r.per_class = (r.n_items + r.deal - 1) / r.deal;
+    r.fd_class = ws::fastdiv_make((uint32_t)r.per_class);
+    return true;
 }
 
 // Partials are kept in blocks of 32 packed rows per (stream, KV head).
@@ -759,10 +903,20 @@ int step_impl(ws_tensor4 q, ws_tensor4 k_new, ws_tensor4 v_new, const ws_paged_k
         }
     }
     if (!finish_work(a)) return fail(WS_ERR_SHAPE, "too many work items");
-    if (int e = ws::launch_attention(a, kv->head_dim, plan.shape, stream))
+    // streams of different lengths: per-stream splits
+    ws::RaggedPlan rag;
+    const bool ragged = plan_ragged(rag, cus, plan, batch, num_q_heads, kv->num_kv_heads, new_len, cache_lens_host,
+                                    nl_host, text_host);
+    if (ragged) {
+        a.per_group = rag.deal * rag.per_class;
+        a.fd_group = ws::fastdiv_make((uint32_t)a.per_group);
+        a.n_work = a.Hkv * a.per_group;
+        a.per_xcd = (a.n_work + ws::NUM_XCD - 1) / ws::NUM_XCD;
+    }
+    if (int e = ws::launch_attention(a, ragged ? &rag : nullptr, kv->head_dim, plan.shape, stream))
         return fail(WS_ERR_HIP, "attention launch failed (hip error %d)", e);
-    if (plan.nsplit > 1)
-        if (int e = ws::launch_combine(a, kv->head_dim, stream))
+    if ((ragged ? rag.max_nsplit : plan.nsplit) > 1)
+        if (int e = ws::launch_combine(a, ragged ? &rag : nullptr, kv->head_dim, stream))
             return fail(WS_ERR_HIP, "combine launch failed (hip error %d)", e);
     return ok();
 }
@@ -846,7 +1000,7 @@ int prefill_impl(ws_tensor4 q, ws_tensor4 k, ws_tensor4 v, const ws_paged_kv *kv
     a.nqt = (seq_len + shape.qtile() - 1) / shape.qtile();
     a.scale_log2 = scale * 1.4426950408889634f;
     if (!finish_work(a)) return fail(WS_ERR_SHAPE, "too many work items");
-    if (int e = ws::launch_attention(a, head_dim, shape, stream))
+    if (int e = ws::launch_attention(a, nullptr, head_dim, shape, stream))
         return fail(WS_ERR_HIP, "prefill launch failed (hip error %d)", e);
     return ok();
 }

@@ -77,12 +77,13 @@ struct AttnArgs {
     // row p = t * G + hh for token t and head kvh * G + hh, so small blocks
     // still fill the query tiles; nrows = G * Lq rows per (b, KV head).
     // split-KV partials (step only), in blocks of 32 packed rows (nrb =
-    // ceil(G * Lq / 32) blocks per (b, KV head)).  f32 output: o
-    // [S][B][Hkv][nrb][D/4][64 lanes][4] f32 unnormalised, in the
-    // accumulator's register order, and (m, l) [S][B][Hkv][nrb * 32][2].
-    // bf16 output: o / l as bf16 [S][B][Hkv][nrb][D/8][64 lanes][8] in
+    // ceil(G * Lq / 32) blocks per (b, KV head)); a split of a stream has a
+    // slot: the stream's first slot (b * nsplit, or slot_arg) + split.  f32
+    // output: o [slot][Hkv][nrb][D/4][64 lanes][4] f32 unnormalised, in the
+    // accumulator's register order, and (m, l) [slot][Hkv][nrb * 32][2].
+    // bf16 output: o / l as bf16 [slot][Hkv][nrb][D/8][64 lanes][8] in
     // register order (two accumulator groups per lane) and m + log2(l)
-    // [S][B][Hkv][nrb * 32] f32 at part_ml.
+    // [slot][Hkv][nrb * 32] f32 at part_ml.
     float *part_o, *part_ml;
     int32_t nrb;
     int32_t nrows;       // rows per item's head space: Lq (prefill) or G * Lq (step)
@@ -112,6 +113,33 @@ struct AttnArgs {
 };
 
 constexpr int LENS_IN_ARGS = 32;
+
+// A step over at most LENS_IN_ARGS streams of different lengths, each with
+// its own split count (beside the AttnArgs, whose plan fields n_work, per_xcd,
+// per_group and fd_group then count these items).  The items of a KV head are
+// stream by stream, longest first: (query tiles with real rows) x (splits).
+// They are dealt out to `deal` classes of per_class items (item = j * deal +
+// class), and the launch runs KV head by KV head, class by class, so that the
+// contiguous range of items each XCD takes is a whole number of classes: an
+// even share of every stream.
+struct RaggedStream {
+    int32_t start;      // first item (INT32_MAX past the last stream)
+    int32_t b;          // the stream
+    int32_t ns;         // its splits
+    int32_t slot;       // its first partial slot (unused when ns is 1)
+    int32_t n_pool, nl, text;   // its cache length, block length, segment start
+    int32_t items;      // its items: tiles x ns
+    FastDiv fd_ns;
+    int32_t pad[2];     // (three 16-byte loads per lane)
+};
+struct RaggedPlan {
+    int32_t n_items;    // items of one KV head
+    int32_t deal, per_class;
+    FastDiv fd_class;   // divider by per_class
+    int32_t max_nsplit;
+    RaggedStream pos[LENS_IN_ARGS];
+    int32_t ns[LENS_IN_ARGS], slot[LENS_IN_ARGS];   // by stream, for the merge
+};
 
 struct AppendArgs {
     const uint16_t *kn, *vn;
@@ -177,8 +205,9 @@ struct TileShape {
 };
 
 // Each returns 0 or a HIP error code (hipError_t as int).
-int launch_attention(const AttnArgs &a, int head_dim, TileShape shape, void *stream);
-int launch_combine(const AttnArgs &a, int head_dim, void *stream);
+// (rag: per-stream splits, or nullptr for one split count)
+int launch_attention(const AttnArgs &a, const RaggedPlan *rag, int head_dim, TileShape shape, void *stream);
+int launch_combine(const AttnArgs &a, const RaggedPlan *rag, int head_dim, void *stream);
 int launch_append(const AppendArgs &a, void *stream);
 // dQ (with the row data), then dK/dV and the sum of its parts; 0 or a HIP error code
 int launch_prefill_bwd(const BwdArgs &a, int head_dim, void *stream);

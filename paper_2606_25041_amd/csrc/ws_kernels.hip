@@ -44,6 +44,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "ws_kernels.h"
 #include "ws_device_util.h"
 
@@ -56,14 +58,13 @@ constexpr float RESCALE_BOUND = 256.f;  // 2^RESCALE_LOG2
 constexpr int NSTAGE = 5;            // K/V tiles resident in the LDS ring (loads three tiles ahead)
 constexpr int RAHEAD = 4;            // LDS operand reads issued this many MFMAs ahead
 
-// The fused append's share of step work item ai (of nqt * nsplit per
-// (stream, KV head)): the group's items split the new tokens evenly; tokens
-// t >= nl are padding and not committed.  One 16-byte chunk per thread.
+// The fused append's share of step work item ai of the napp items of its
+// (stream, KV head): they split the new tokens evenly; tokens t >= nl are
+// padding and not committed.  One 16-byte chunk per thread.
 template <int D, int NT>
-__device__ __forceinline__ void append_share(const AttnArgs &a, int b, int kvh, int ai, int n_pool, int nl,
+__device__ __forceinline__ void append_share(const AttnArgs &a, int b, int kvh, int ai, int napp, int n_pool, int nl,
                                              const int32_t *ptab, int tid) {
     constexpr int CH = D / 8;
-    const int napp = a.nqt * a.nsplit;
     const int s0 = (int)((int64_t)ai * a.Lq / napp);
     const int n = max(min((int)((int64_t)(ai + 1) * a.Lq / napp), nl) - s0, 0) * CH;
     for (int u = tid; u < n; u += NT) {
@@ -79,11 +80,17 @@ __device__ __forceinline__ void append_share(const AttnArgs &a, int b, int kvh, 
 // call carries none of the others' scalars through its loop (the contiguous
 // prefill read its tile bases back from spilled registers) nor their code
 // through the instruction cache, where short launches spend their time.
-enum Kind { PREFILL_CONTIGUOUS, PREFILL_PAGED, STEP };
+enum Kind { PREFILL_CONTIGUOUS, PREFILL_PAGED, STEP, STEP_RAGGED };
+
+// STEP_RAGGED: the streams have their own split counts (rp).
+struct NoPlan {};
+template <bool RAGGED>
+using Plan = std::conditional_t<RAGGED, RaggedPlan, NoPlan>;
 
 template <int D, int NW, int NB, int KIND, bool F32>
-__global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a) {
-    constexpr bool step = KIND == STEP;
+__global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const Plan<KIND == STEP_RAGGED> rp) {
+    constexpr bool step = KIND == STEP || KIND == STEP_RAGGED;
+    constexpr bool RAGGED = KIND == STEP_RAGGED;
     constexpr int NT = NW * 64;
     constexpr int QT = NW * 32 * NB;       // query rows per work-group
     constexpr int ROWB = 2 * D;            // bytes of one key row
@@ -116,25 +123,50 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a) {
                       "+s"(fd_qt.mul), "+s"(fd_qt.shift), "+s"(fd_g.mul), "+s"(fd_g.shift), "+s"(fd_hkv.mul),
                       "+s"(fd_hkv.shift), "+s"(fd_split.mul), "+s"(fd_split.shift), "+s"(fd_gq.mul),
                       "+s"(fd_gq.shift), "+s"(qptr), "+s"(q_sb), "+s"(q_st), "+s"(q_sh), "+s"(has_nl));
+    // Ragged: lane p of each half-wave reads plan position p in the same
+    // round trip; the item's stream is then picked by a ballot and its fields
+    // by lane reads, so no load depends on the item.
+    i32x4 pos[3];
+    if constexpr (RAGGED) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) pos[i] = ((const i32x4 *)&rp.pos[threadIdx.x & 31])[i];
+        asm volatile("" : "+v"(pos[0]), "+v"(pos[1]), "+v"(pos[2]));
+    }
     const uint32_t w = (bid % NUM_XCD) * per_xcd + bid / NUM_XCD;
     if (w >= n_work) return;
     const uint32_t group = fastdiv(w, fd_group);
-    const uint32_t idx = w - group * per_group;
-    const uint32_t qi = fastdiv(idx, fd_qt);
-    const uint32_t rem = idx - qi * per_qt;
-    const uint32_t split = fastdiv(rem, fd_g);
-    const int hh = (int)(rem - split * gi);
-    // Groups are taken stream-major; a step over blocks of different lengths
-    // takes them KV-head-major instead, so that the contiguous range of items
-    // each XCD runs mixes long and short streams rather than holding a few
-    // streams only.
-    int b, kvh;
-    if (has_nl) {
-        kvh = (int)fastdiv(group, a.fd_b);
-        b = (int)(group - (uint32_t)kvh * (uint32_t)a.B);
+    uint32_t idx = w - group * per_group;
+    uint32_t qi, split;
+    int b, kvh, hh = 0, ppos = 0;
+    auto field = [&](int i) -> int { return __builtin_amdgcn_readlane(pos[i >> 2][i & 3], ppos); };
+    if constexpr (RAGGED) {
+        kvh = (int)group;
+        const uint32_t cls = fastdiv(idx, rp.fd_class);
+        idx = (idx - cls * (uint32_t)rp.per_class) * (uint32_t)rp.deal + cls;
+        if (idx >= (uint32_t)rp.n_items) return;
+        ppos = (__builtin_popcountll(__builtin_amdgcn_ballot_w64((uint32_t)pos[0][0] <= idx)) >> 1) - 1;
+        b = field(1);
+        idx -= (uint32_t)field(0);
+        fd_split.mul = (uint32_t)field(8);
+        fd_split.shift = (uint32_t)field(9);
+        qi = fastdiv(idx, fd_split);
+        split = idx - qi * (uint32_t)field(2);
     } else {
-        b = (int)fastdiv(group, fd_hkv);
-        kvh = (int)(group - b * Hkv);
+        qi = fastdiv(idx, fd_qt);
+        const uint32_t rem = idx - qi * per_qt;
+        split = fastdiv(rem, fd_g);
+        hh = (int)(rem - split * gi);
+        // Groups are taken stream-major; a step over blocks of different
+        // lengths takes them KV-head-major instead, so that the contiguous
+        // range of items each XCD runs mixes long and short streams rather
+        // than holding a few streams only.
+        if (has_nl) {
+            kvh = (int)fastdiv(group, a.fd_b);
+            b = (int)(group - (uint32_t)kvh * (uint32_t)a.B);
+        } else {
+            b = (int)fastdiv(group, fd_hkv);
+            kvh = (int)(group - b * Hkv);
+        }
     }
     const int hq = kvh * (int)G + hh;   // (prefill; a step's rows span the group's heads)
     // token and query head of packed row p (see AttnArgs)
@@ -157,12 +189,12 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a) {
     // of different lengths, padded) holds no real row: it computes nothing
     // and leaves its rows' outputs unwritten, but still does its share of
     // the fused append.  Decided before any load is issued.
-    if (step && has_nl) {
+    if (!RAGGED && step && has_nl) {
         const int nl0 = a.lens_in_args ? a.nl_arg[b] : ld_uniform(a.new_lens, b);
         if ((int)fastdiv((uint32_t)q0, fd_gq) >= nl0) {
             if (a.fuse_append) {
                 const int np0 = a.lens_in_args ? a.lens_arg[b] : ld_uniform(a.cache_lens, b);
-                append_share<D, NT>(a, b, kvh, (int)(qi * a.nsplit + split), np0, nl0,
+                append_share<D, NT>(a, b, kvh, (int)(qi * a.nsplit + split), a.nqt * a.nsplit, np0, nl0,
                                     a.page_table + (int64_t)b * a.max_pages, tid);
             }
             return;
@@ -199,13 +231,19 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a) {
     const int32_t *offs = step ? nullptr : a.offsets + (int64_t)b * (a.nb + 1);
     const int32_t *text = (!step && a.has_text) ? a.text_starts + (int64_t)b * a.nb : nullptr;
     int n_pool, k_hi, kfull, ts = 0, nl = 0;
-    if (step) {
+    if constexpr (RAGGED) {
+        n_pool = field(4);
+        nl = field(5);
+        ts = field(6);
+    } else if (step) {
         n_pool = !a.lens_in_args ? ld_uniform(a.cache_lens, b) : b == 0 ? (int)lens0 : a.lens_arg[b];
         // start of the new block's token-causal segment (Lq: none) and the
         // block's length (Lq: no padding); new token t sees
         // n_pool + min(nl, max(ts, t + 1)) keys
         ts = a.lens_in_args ? a.text_arg[b] : a.has_text ? ld_uniform(a.text_starts, b) : a.Lq;
         nl = a.lens_in_args ? a.nl_arg[b] : a.has_new_lens ? ld_uniform(a.new_lens, b) : a.Lq;
+    }
+    if (step) {
         const int t_last = (int)fastdiv((uint32_t)(min(q0 + QT, (int)nrows) - 1), fd_gq);
         k_hi = n_pool + min(nl, max(ts, t_last + 1));
         kfull = n_pool + min(nl, max(ts, (int)fastdiv((uint32_t)q0, fd_gq) + 1));
@@ -632,13 +670,25 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a) {
     }
 
     // ---- epilogue -----------------------------------------------------------
+    // (the plan's fields are read again here rather than held over the loop)
+    int nsplit = 1, slot = 0, napp = 1;
+    if constexpr (RAGGED) {
+        asm volatile("" : "+s"(ppos));
+        nsplit = rp.pos[ppos].ns;
+        slot = rp.pos[ppos].slot + (int)split;
+        napp = rp.pos[ppos].items;
+    } else if constexpr (step) {
+        nsplit = a.nsplit;
+        slot = b * nsplit + (int)split;
+        napp = a.nqt * nsplit;
+    }
     // Output rows of an unsplit item leave through LDS, so that a store covers
     // 16-byte pieces of 4 (D = 64: 8) whole rows rather than of 32: a wave's
     // own query stage holds its 32 rows (f32: half of the head dims at a
     // time), and after the loop's last barrier nothing else touches it.
     // 3.3k tokens, GQA 40/8 x 128: 136 -> 131 us; GQA 64/8, 2 x 1.4k: 118 ->
     // 112 us; unchanged where an item runs many tiles.
-    if ((!step || a.nsplit == 1) && busy) {
+    if ((!step || nsplit == 1) && busy) {
         // (the lane is hidden from the optimiser, so that nothing derived from
         // it here is computed ahead of the loop and held in registers there)
         int ln = lane;
@@ -695,7 +745,7 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a) {
         const int r = row[n];
         if (r >= (int)nrows) continue;
         const int t = tok[n], h = hqr[n];
-        if (!step || a.nsplit == 1) {
+        if (!step || nsplit == 1) {
             if (a.lse && hf == 0)
                 a.lse[((int64_t)b * a.Hq + h) * a.Lq + t] = (m[n] + __builtin_amdgcn_logf(lt)) * 0.69314718055994531f;
         } else if constexpr (!F32) {
@@ -704,7 +754,7 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a) {
             // lane, so each store instruction writes 1 KB contiguous.
             // Partials are stored non-temporally (read once, by the combine
             // launch)
-            const int64_t blk = (((int64_t)split * a.B + b) * a.Hkv + kvh) * a.nrb + (r >> 5);
+            const int64_t blk = ((int64_t)slot * a.Hkv + kvh) * a.nrb + (r >> 5);
             const float inv = lt > 0.f ? 1.f / lt : 0.f;
             uint16_t *op = (uint16_t *)a.part_o + blk * (32 * D) + 8 * lane;
 #pragma unroll
@@ -721,7 +771,7 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a) {
             if (hf == 0) __builtin_nontemporal_store(lt > 0.f ? m[n] + __builtin_amdgcn_logf(lt) : -INFINITY, a.part_ml + blk * 32 + l32);
         } else {
             // register order: each store instruction writes 1 KB contiguous
-            const int64_t blk = (((int64_t)split * a.B + b) * a.Hkv + kvh) * a.nrb + (r >> 5);
+            const int64_t blk = ((int64_t)slot * a.Hkv + kvh) * a.nrb + (r >> 5);
             float *op = a.part_o + blk * (32 * D) + 4 * lane;
 #pragma unroll
             for (int md = 0; md < MD; ++md)
@@ -747,7 +797,7 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a) {
     // written, so the append can trail the attention; it comes after the
     // epilogue's stores so that its loads overlap their drain.
     if (step && a.fuse_append && hh == 0)
-        append_share<D, NT>(a, b, kvh, (int)(qi * a.nsplit + split), n_pool, nl, ptab, tid);
+        append_share<D, NT>(a, b, kvh, (int)(qi * nsplit + split), napp, n_pool, nl, ptab, tid);
 }
 
 // bf16 output: split s holds o_s / l_s (bf16) and lse_s = m_s + log2(l_s);
@@ -759,8 +809,10 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a) {
 // SMAX times (the launch takes the smallest of 8, 16, 32, which also keeps
 // the register count, and with it the waves per SIMD that hide the loads'
 // latency, down).
-template <int D, bool VARLEN, int SMAX>
-__global__ __launch_bounds__(256) void combine16_kernel(const AttnArgs a) {
+// RAGGED: the streams have their own split counts and slots (rp); a stream
+// with one split was written by the attention launch.
+template <int D, bool VARLEN, bool RAGGED, int SMAX>
+__global__ __launch_bounds__(256) void combine16_kernel(const AttnArgs a, const Plan<RAGGED> rp) {
     static_assert(SMAX <= MAX_SPLITS, "at most MAX_SPLITS partials");
     constexpr int MD = D / 32;
     constexpr int PER_BLK = 2 * MD * 64;      // 16-byte items per 32-row block
@@ -778,11 +830,18 @@ __global__ __launch_bounds__(256) void combine16_kernel(const AttnArgs a) {
     const int t = r / a.G;
     if (VARLEN && t >= a.new_lens[b]) return;   // padding row: left unwritten
     const int hq = kvh * a.G + (r - t * a.G);
-    const int S = a.nsplit;
-    const float *pl = a.part_ml + blk * 32 + (lane & 31);
-    const uint16_t *po = (const uint16_t *)a.part_o + blk * (32 * D) + pg * 512 + 8 * lane;
-    const int64_t ls = nblk * 32;             // split stride of lse
-    const int64_t ps = nblk * 32 * D;         // split stride of o
+    int S = a.nsplit, slot = b * S;
+    if constexpr (RAGGED) {
+        S = rp.ns[b];
+        slot = rp.slot[b];
+        if (S == 1) return;
+    }
+    const int64_t sb = (int64_t)a.Hkv * a.nrb;   // blocks per slot
+    const int64_t pb = slot * sb + (blk - b * sb);
+    const float *pl = a.part_ml + pb * 32 + (lane & 31);
+    const uint16_t *po = (const uint16_t *)a.part_o + pb * (32 * D) + pg * 512 + 8 * lane;
+    const int64_t ls = sb * 32;               // split stride of lse
+    const int64_t ps = sb * 32 * D;           // split stride of o
     // all loads first (one round trip), then the arithmetic
     float lse[SMAX];
     u32x4 ov[SMAX];
@@ -832,9 +891,11 @@ __global__ __launch_bounds__(256) void combine16_kernel(const AttnArgs a) {
 // Splits are visited in a fixed order, so the result is deterministic.  A
 // thread owns the 4 elements one accumulator lane holds for one (md, g), so
 // its partial reads are the writer's contiguous 1 KB runs; the split loops
-// are unrolled so their independent loads are in flight together.
-template <int D, bool VARLEN>
-__global__ __launch_bounds__(256) void combine_kernel(const AttnArgs a) {
+// are unrolled (as in combine16_kernel), so that all loads are in flight
+// together: 20 splits of 240 blocks, head dim 64: 11.3 us as a rolled loop
+// over the splits.
+template <int D, bool VARLEN, bool RAGGED, int SMAX>
+__global__ __launch_bounds__(256) void combine_kernel(const AttnArgs a, const Plan<RAGGED> rp) {
     constexpr int MD = D / 32;
     constexpr int PER_BLK = MD * 4 * 64;      // float4 items per 32-row block
     const int64_t nblk = (int64_t)a.B * a.Hkv * a.nrb;
@@ -852,40 +913,50 @@ __global__ __launch_bounds__(256) void combine_kernel(const AttnArgs a) {
     if (VARLEN && t >= a.new_lens[b]) return;   // padding row: left unwritten
     const int hq = kvh * a.G + (r - t * a.G);
     const int d0 = 32 * (mg >> 2) + 8 * (mg & 3) + 4 * (lane >> 5);
-    const int S = a.nsplit;
-    const float2 *ml = (const float2 *)a.part_ml + blk * 32 + (lane & 31);
-    const float *po = a.part_o + blk * (32 * D) + (int64_t)mg * 256 + 4 * lane;
-    const int64_t mls = nblk * 32;            // split stride of (m, l)
-    const int64_t ps = nblk * 32 * D;         // split stride of o
+    int S = a.nsplit, slot = b * S;
+    if constexpr (RAGGED) {
+        S = rp.ns[b];
+        slot = rp.slot[b];
+        if (S == 1) return;
+    }
+    const int64_t sb = (int64_t)a.Hkv * a.nrb;   // blocks per slot
+    const int64_t pb = slot * sb + (blk - b * sb);
+    const float2 *ml = (const float2 *)a.part_ml + pb * 32 + (lane & 31);
+    const float *po = a.part_o + pb * (32 * D) + (int64_t)mg * 256 + 4 * lane;
+    const int64_t mls = sb * 32;              // split stride of (m, l)
+    const int64_t ps = sb * 32 * D;           // split stride of o
+    // all loads first (one round trip), then the arithmetic
+    float2 m_l[SMAX];
+    f32x4 ov[SMAX];
+#pragma unroll
+    for (int s = 0; s < SMAX; ++s) {
+        if (s < S) {
+            m_l[s] = ml[s * mls];
+            ov[s] = *(const f32x4 *)(po + s * ps);
+        } else {
+            m_l[s] = float2{-INFINITY, 0.f};
+            ov[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
     float M = -INFINITY;
-#pragma unroll 8
-    for (int s = 0; s < S; ++s) M = fmaxf(M, ml[s * mls].x);
+#pragma unroll
+    for (int s = 0; s < SMAX; ++s) M = fmaxf(M, m_l[s].x);
     const float Mu = (M == -INFINITY) ? 0.f : M;
     float L = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int s = 0; s < S; ++s) {
-        const float2 m_l = ml[s * mls];
-        const f32x4 ov = *(const f32x4 *)(po + s * ps);
-        const float wgt = __builtin_amdgcn_exp2f(m_l.x - Mu);
-        L += m_l.y * wgt;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] += ov[e] * wgt;
+    for (int s = 0; s < SMAX; ++s) {
+        const float wgt = __builtin_amdgcn_exp2f(m_l[s].x - Mu);   // 0 for absent splits
+        L += m_l[s].y * wgt;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += ov[s][e] * wgt;
     }
     const float inv = L > 0.f ? 1.f / L : 0.f;
-    if (a.out_f32) {
-        float *op = (float *)a.out + b * a.o_sb + (int64_t)t * a.o_st + hq * a.o_sh + d0;
-        f32x4 val;
+    float *op = (float *)a.out + b * a.o_sb + (int64_t)t * a.o_st + hq * a.o_sh + d0;
+    f32x4 val;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) val[e] = acc[e] * inv;
-        *(f32x4 *)op = val;
-    } else {
-        uint16_t *op = (uint16_t *)a.out + b * a.o_sb + (int64_t)t * a.o_st + hq * a.o_sh + d0;
-        u32x2 val;
-        val[0] = pack_bf16x2(acc[0] * inv, acc[1] * inv);
-        val[1] = pack_bf16x2(acc[2] * inv, acc[3] * inv);
-        *(u32x2 *)op = val;
-    }
+    for (int e = 0; e < 4; ++e) val[e] = acc[e] * inv;
+    *(f32x4 *)op = val;
     if (a.lse && mg == 0 && lane < 32)
         a.lse[((int64_t)b * a.Hq + hq) * a.Lq + t] = (M + __builtin_amdgcn_logf(L)) * 0.69314718055994531f;
 }
@@ -910,57 +981,64 @@ __global__ __launch_bounds__(256) void append_kernel(const AppendArgs a) {
 }
 
 template <int D, int KIND>
-int launch_attn_t(const AttnArgs &a, hipStream_t st) {
+int launch_attn_t(const AttnArgs &a, const Plan<KIND == STEP_RAGGED> &rp, hipStream_t st) {
     const dim3 grid(a.per_xcd * NUM_XCD), block(8 * 64);
     if (a.out_f32)
-        hipLaunchKernelGGL((attn_kernel<D, 8, 1, KIND, true>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((attn_kernel<D, 8, 1, KIND, true>), grid, block, 0, st, a, rp);
     else
-        hipLaunchKernelGGL((attn_kernel<D, 8, 1, KIND, false>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((attn_kernel<D, 8, 1, KIND, false>), grid, block, 0, st, a, rp);
     return (int)hipGetLastError();
 }
 
 template <int D>
-int launch_attn_d(const AttnArgs &a, hipStream_t st) {
-    return a.mode == MODE_STEP ? launch_attn_t<D, STEP>(a, st)
-         : a.paged ? launch_attn_t<D, PREFILL_PAGED>(a, st) : launch_attn_t<D, PREFILL_CONTIGUOUS>(a, st);
+int launch_attn_d(const AttnArgs &a, const RaggedPlan *rag, hipStream_t st) {
+    return rag ? launch_attn_t<D, STEP_RAGGED>(a, *rag, st)
+         : a.mode == MODE_STEP ? launch_attn_t<D, STEP>(a, NoPlan{}, st)
+         : a.paged ? launch_attn_t<D, PREFILL_PAGED>(a, NoPlan{}, st)
+                   : launch_attn_t<D, PREFILL_CONTIGUOUS>(a, NoPlan{}, st);
+}
+
+template <int D, bool VL, bool RAGGED>
+int launch_combine_t(const AttnArgs &a, const Plan<RAGGED> &rp, int nsplit, hipStream_t st) {
+    const int64_t per_blk = (int64_t)(D / 32) * (a.out_f32 ? 4 : 2) * 64;   // items per 32-row block
+    const dim3 grid((unsigned)(((int64_t)a.B * a.Hkv * a.nrb * per_blk + 255) / 256));
+    auto launch = [&](auto smax) {
+        constexpr int SMAX = decltype(smax)::value;
+        if (a.out_f32)
+            hipLaunchKernelGGL((combine_kernel<D, VL, RAGGED, SMAX>), grid, dim3(256), 0, st, a, rp);
+        else
+            hipLaunchKernelGGL((combine16_kernel<D, VL, RAGGED, SMAX>), grid, dim3(256), 0, st, a, rp);
+    };
+    if (nsplit <= 8) launch(std::integral_constant<int, 8>{});
+    else if (nsplit <= 16) launch(std::integral_constant<int, 16>{});
+    else launch(std::integral_constant<int, MAX_SPLITS>{});
+    return (int)hipGetLastError();
+}
+
+template <int D>
+int launch_combine_d(const AttnArgs &a, const RaggedPlan *rag, hipStream_t st) {
+    if (rag)
+        return a.has_new_lens ? launch_combine_t<D, true, true>(a, *rag, rag->max_nsplit, st)
+                              : launch_combine_t<D, false, true>(a, *rag, rag->max_nsplit, st);
+    return a.has_new_lens ? launch_combine_t<D, true, false>(a, NoPlan{}, a.nsplit, st)
+                          : launch_combine_t<D, false, false>(a, NoPlan{}, a.nsplit, st);
 }
 
 }  // namespace
 
-int launch_attention(const AttnArgs &a, int head_dim, TileShape shape, void *stream) {
+int launch_attention(const AttnArgs &a, const RaggedPlan *rag, int head_dim, TileShape shape, void *stream) {
     hipStream_t st = (hipStream_t)stream;
     if (shape.nw != 8 || shape.nb != 1) return (int)hipErrorInvalidValue;
-    if (head_dim == 128) return launch_attn_d<128>(a, st);
-    if (head_dim == 64) return launch_attn_d<64>(a, st);
+    if (head_dim == 128) return launch_attn_d<128>(a, rag, st);
+    if (head_dim == 64) return launch_attn_d<64>(a, rag, st);
     return (int)hipErrorInvalidValue;
 }
 
-typedef void (*CombineKern)(const AttnArgs);
-
-template <int D, bool VL>
-CombineKern combine16_for(int nsplit) {
-    return nsplit <= 8 ? combine16_kernel<D, VL, 8>
-         : nsplit <= 16 ? combine16_kernel<D, VL, 16> : combine16_kernel<D, VL, MAX_SPLITS>;
-}
-
-int launch_combine(const AttnArgs &a, int head_dim, void *stream) {
+int launch_combine(const AttnArgs &a, const RaggedPlan *rag, int head_dim, void *stream) {
     hipStream_t st = (hipStream_t)stream;
-    typedef CombineKern Kern;
-    const bool vl = a.has_new_lens != 0;
-    if (!a.out_f32) {
-        const int64_t items = (int64_t)a.B * a.Hkv * a.nrb * (head_dim / 32) * 2 * 64;
-        const int64_t grid = (items + 255) / 256;
-        Kern k = head_dim == 128 ? (vl ? combine16_for<128, true>(a.nsplit) : combine16_for<128, false>(a.nsplit))
-                                 : (vl ? combine16_for<64, true>(a.nsplit) : combine16_for<64, false>(a.nsplit));
-        hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(256), 0, st, a);
-        return (int)hipGetLastError();
-    }
-    const int64_t items = (int64_t)a.B * a.Hkv * a.nrb * (head_dim / 32) * 4 * 64;
-    const int64_t grid = (items + 255) / 256;
-    Kern k = head_dim == 128 ? (vl ? combine_kernel<128, true> : combine_kernel<128, false>)
-                             : (vl ? combine_kernel<64, true> : combine_kernel<64, false>);
-    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(256), 0, st, a);
-    return (int)hipGetLastError();
+    if (head_dim == 128) return launch_combine_d<128>(a, rag, st);
+    if (head_dim == 64) return launch_combine_d<64>(a, rag, st);
+    return (int)hipErrorInvalidValue;
 }
 
 int launch_append(const AppendArgs &a, void *stream) {
