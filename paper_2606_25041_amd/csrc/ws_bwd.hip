@@ -119,9 +119,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int rc = min(row, a.L - 1);
     const int32_t *offs = a.offsets + (int64_t)b * (a.nb + 1);
     const int32_t *text = a.text_starts ? a.text_starts + (int64_t)b * a.nb : nullptr;
-    const int k_hi = row_key_end<true>(offs, text, a.nb, min(q0 + 127, a.L - 1));
-    const int kfull = row_key_end<true>(offs, text, a.nb, q0);
-    const int my_kend = row_key_end<false>(offs, text, a.nb, rc);
+    const BlockWindow win = block_window(offs, text, a.nb, q0, lane);
+    const int k_hi = token_key_end(win, min(q0 + 127, a.L - 1), lane);
+    const int kfull = token_key_end(win, q0, lane);
+    const int my_kend = lane_key_end(win, min(q0 + 32 * wave, a.L - 1), rc, lane);
     const float lse2 = a.lse[((int64_t)b * a.Hq + h) * a.L + rc] * 1.4426950408889634f;
     const float c2 = a.scale_log2;
 

@@ -231,6 +231,7 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
     const int32_t *offs = step ? nullptr : a.offsets + (int64_t)b * (a.nb + 1);
     const int32_t *text = (!step && a.has_text) ? a.text_starts + (int64_t)b * a.nb : nullptr;
     int n_pool, k_hi, kfull, ts = 0, nl = 0;
+    BlockWindow win;   // (prefill)
     if constexpr (RAGGED) {
         n_pool = field(4);
         nl = field(5);
@@ -250,8 +251,9 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
     } else {
         n_pool = KIND == PREFILL_PAGED ? a.Lq : 0;
         const int q_last = min(q0 + QT, a.Lq) - 1;
-        k_hi = row_key_end<true>(offs, text, a.nb, q_last);
-        kfull = row_key_end<true>(offs, text, a.nb, q0);
+        win = block_window(offs, text, a.nb, q0, lane);
+        k_hi = token_key_end(win, q_last, lane);
+        kfull = token_key_end(win, q0, lane);
     }
     const int ntile = (k_hi + KT - 1) / KT;
     // (split * ntile < 2^31: ntile < 2^25 and split < MAX_SPLITS = 32)
@@ -277,7 +279,8 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
         const int pc = min(row[n], (int)nrows - 1);
         tok[n] = row_token(pc);
         hqr[n] = row_head(pc, tok[n]);
-        kend[n] = step ? n_pool + min(nl, max(ts, tok[n] + 1)) : row_key_end<false>(offs, text, a.nb, tok[n]);
+        if constexpr (step) kend[n] = n_pool + min(nl, max(ts, tok[n] + 1));
+        else kend[n] = lane_key_end(win, min(q0 + rblk * 32 * NB + 32 * n, (int)nrows - 1), tok[n], lane);
     }
 
     // ---- direct-to-LDS tile loads -----------------------------------------
