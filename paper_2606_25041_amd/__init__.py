@@ -1,9 +1,11 @@
 """Block-causal streaming attention on MI355X (gfx950).
 
-Thin ctypes binding over libwsattn.so (C ABI in include/ws_attn.h).  Python
-only marshals arguments: every step of the computation runs in the HIP
-kernels of csrc/.  PyTorch supplies device memory and the current stream.
-If the library is missing this module raises; there is no fallback.
+Thin binding over libwsattn.so (C ABI in include/ws_attn.h).  Python only
+marshals arguments: every step of the computation runs in the HIP kernels of
+csrc/.  PyTorch supplies device memory and the current stream.  If the library
+is missing this module raises; there is no fallback.  The entry points marshal
+the common case natively (csrc/ws_binding.cpp, same C ABI); what that declines
+goes through the ctypes code here, which holds the checks and their errors.
 
 Entry points (same names as the C ABI, without the ``ws_`` prefix):
   kv_append(cache, cache_lens, k_new, v_new, new_lens=None)
@@ -64,6 +66,7 @@ class PagedKVDesc(ctypes.Structure):
 
 
 _LIB = None
+_NATIVE = None
 
 
 def library():
@@ -119,8 +122,30 @@ def library():
                                      ctypes.POINTER(ctypes.c_size_t)]
         if lib.ws_abi_version() != 5:
             raise RuntimeError("libwsattn.so ABI version mismatch")
+        _bind_native(lib)
         _LIB = lib
     return _LIB
+
+
+def _bind_native(lib):
+    """Loads the native marshalling and hands it the library's functions."""
+    global _NATIVE
+    if _NATIVE is None:
+        if not os.path.exists(_build.BINDING):
+            raise RuntimeError(f"{_build.BINDING} is not built; run `python -m paper_2606_25041_amd.build`")
+        from . import _wsbinding
+        _NATIVE = _wsbinding
+    _NATIVE.bind(*(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in (
+        "ws_kv_append", "ws_kv_append_varlen", "ws_block_causal_attn_fwd", "ws_block_causal_attn_fwd_text",
+        "ws_block_causal_attn_fwd_varlen", "ws_block_causal_attn_fwd_noalloc", "ws_block_causal_prefill",
+        "ws_block_causal_prefill_text", "ws_block_causal_prefill_bwd", "ws_workspace_bytes",
+        "ws_step_workspace_bytes_varlen")))
+
+
+def _native():
+    if _LIB is None:
+        library()
+    return _NATIVE
 
 
 def abi_version():
@@ -244,6 +269,11 @@ def step_plan(batch, num_q_heads, num_kv_heads, new_len, cache_lens, new_lens=No
 def kv_append(cache, cache_lens, k_new, v_new, new_lens=None):
     """Commit k_new/v_new [B][Ln][Hkv][d] at positions cache_lens[b] + t
     (only t < new_lens[b] when new_lens, [B], is given)."""
+    rc = _native().append(cache, cache_lens, k_new, v_new, new_lens)
+    if rc is not None:
+        if rc:
+            _check(rc)
+        return
     host, dev = _lens(cache_lens, k_new.device)
     B, Ln = k_new.shape[0], k_new.shape[1]
     _shape("k_new", k_new, (B, Ln, cache.num_kv_heads, cache.head_dim))
@@ -288,6 +318,13 @@ def block_causal_attn_fwd(q, k_new, v_new, cache, cache_lens, scale=None, fuse_a
     new_lens[b] tokens; the rest is padding, never a key and never committed,
     and its rows' out and lse are unspecified.
     Returns out (and lse [B][Hq][Lq] f32 when want_lse)."""
+    got = _native().step(q, k_new, v_new, cache, cache_lens, scale, fuse_append, out, out_dtype, want_lse, lse,
+                         workspace, text_starts, new_lens, False)
+    if got is not None:
+        rc, out, lse = got
+        if rc:
+            _check(rc)
+        return (out, lse) if want_lse else out
     B, Lq, Hq, D = q.shape
     host, dev = _lens(cache_lens, q.device)
     if scale is None:
@@ -344,6 +381,13 @@ def block_causal_attn_fwd_noalloc(q, k_new, v_new, cache, cache_lens, out, lse=N
     cache_lens is a (host, device) pair of int32 [B] tensors, out the
     [B][Lq][Hq][d] output (bf16 or f32), lse None or f32 [B][Hq][Lq].
     Calls on one device must be ordered (they share the scratch array)."""
+    if out is not None:
+        got = _native().step(q, k_new, v_new, cache, cache_lens, scale, fuse_append, out, None, False, lse, None, None,
+                             None, True)
+        if got is not None:
+            if got[0]:
+                _check(got[0])
+            return out
     B, Lq, Hq, D = q.shape
     if not isinstance(cache_lens, tuple):
         raise ValueError("cache_lens must be a (host, device) pair of int32 tensors")
@@ -374,6 +418,13 @@ def block_causal_prefill(q, k, v, block_offsets, scale=None, cache=None, num_kv_
     (optional, [B][nb], absolute positions): block n ends in a token-causal
     segment starting there; its token i then sees keys
     j < max(text_starts[b][n], i + 1)."""
+    got = _native().prefill(q, k, v, block_offsets, scale, cache, num_kv_heads, out, out_dtype, want_lse, lse,
+                            text_starts)
+    if got is not None:
+        rc, out, lse = got
+        if rc:
+            _check(rc)
+        return (out, lse) if want_lse else out
     B, L, Hq, D = q.shape
     if isinstance(block_offsets, tuple):
         off_h, off_d = block_offsets
@@ -420,6 +471,11 @@ def block_causal_prefill_bwd(q, k, v, o, dout, lse, block_offsets, scale=None, t
     output gradient dout: returns f32 (dq [B][L][Hq][d], dk, dv
     [B][L][Hkv][d]).  o and lse are the forward's output and lse;
     text_starts as in ``block_causal_prefill``."""
+    got = _native().prefill_bwd(q, k, v, o, dout, lse, block_offsets, scale, text_starts, dq, dk, dv, workspace)
+    if got is not None:
+        if got[0]:
+            _check(got[0])
+        return got[1:]
     B, L, Hq, D = q.shape
     hkv = k.shape[2]
     if isinstance(block_offsets, tuple):

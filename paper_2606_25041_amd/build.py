@@ -12,7 +12,7 @@ LIB = os.path.join(HERE, "libwsattn.so")
 DEVICE_SOURCES = [os.path.join(CSRC, "ws_kernels.hip"), os.path.join(CSRC, "ws_bwd.hip"),
                   os.path.join(CSRC, "ws_device.hip")]
 HOST_SOURCES = [os.path.join(CSRC, "ws_api.cpp")]
-SOURCES = DEVICE_SOURCES + HOST_SOURCES
+SOURCES = DEVICE_SOURCES + HOST_SOURCES + [os.path.join(CSRC, "ws_binding.cpp")]
 HEADERS = [os.path.join(CSRC, "ws_kernels.h"), os.path.join(CSRC, "ws_device_util.h"),
            os.path.join(os.path.dirname(HERE), "include", "ws_attn.h")]
 # the device code whose hash tags measured counter summaries: the forward
@@ -47,13 +47,38 @@ def _run(cmd):
     return msgs
 
 
+# the CPython marshalling of the entry points (compiled against torch)
+BINDING_SRC = os.path.join(CSRC, "ws_binding.cpp")
+BINDING = os.path.join(HERE, "_wsbinding.so")
+
+
+def build_binding(verbose=False):
+    """The package's native marshalling, as the extension module _wsbinding."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    msgs = _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                 f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                 "-isystem", os.path.join(root, "include"),
+                 "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                 "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
+                 BINDING_SRC, "-o", BINDING + ".tmp", "-L", os.path.join(root, "lib"),
+                 "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"])
+    if verbose and msgs:
+        print("\n".join(msgs))
+    os.replace(BINDING + ".tmp", BINDING)
+    return BINDING
+
+
 def build(verbose=False):
     """Kernels (with their device code-generation flags) and the host-only
     C ABI are compiled separately, then linked into one shared library."""
     common = [hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
               "-Wall", "-Wno-unused-function"]
     objs, msgs = [], []
-    for src in SOURCES:
+    for src in DEVICE_SOURCES + HOST_SOURCES:
         obj = LIB + "." + os.path.splitext(os.path.basename(src))[0] + ".o"
         flags = KERNEL_FLAGS if src in DEVICE_SOURCES else []
         msgs += _run(common + flags + ["-c", src, "-o", obj])
@@ -64,6 +89,7 @@ def build(verbose=False):
     if verbose and msgs:
         print("\n".join(msgs))
     os.replace(LIB + ".tmp", LIB)
+    build_binding(verbose)
     return LIB
 
 

@@ -180,22 +180,23 @@ StepPlan plan_step(int num_cus, int batch, int hq, int hkv, int lq, int64_t max_
             return (kvh * pre[batch] + pre[b]) * s + std::min(w - g * P, (pre[b + 1] - pre[b]) * s);
         };
         const int64_t per_cu = std::max<int64_t>(1, slots / ws::NUM_XCD);
-        int64_t rounds = 0;
+        int64_t most = 0, before = 0;
         for (int64_t x = 0; x < ws::NUM_XCD; ++x) {
-            const int64_t c = real_before((x + 1) * per) - real_before(x * per);
-            rounds = std::max(rounds, (c + per_cu - 1) / per_cu);
+            const int64_t to = real_before((x + 1) * per);
+            most = std::max(most, to - before);
+            before = to;
         }
-        return rounds * per_split;
+        return (most + per_cu - 1) / per_cu * per_split;
     };
     if (base > 0) {
         // the fewest splits within 2 % of the modelled minimum (each split
         // adds merge work and thins the L2 reuse of a KV range across q-tiles,
         // which the model leaves out)
-        int64_t lo = cost(1);
-        for (int64_t s = 2; s <= cap; ++s) lo = std::min(lo, cost(s));
-        int64_t best = 1;
-        while (50 * cost(best) > 51 * lo) ++best;
-        if (10 * cost(best) < 9 * cost(ns)) ns = best;
+        int64_t c[WS_MAX_SPLITS + 1], best = 1;
+        for (int64_t s = 1; s <= cap; ++s) c[s] = cost(s);
+        const int64_t lo = *std::min_element(c + 1, c + cap + 1);
+        while (50 * c[best] > 51 * lo) ++best;
+        if (10 * c[best] < 9 * c[ns]) ns = best;
     }
     if (const int s_ov = split_override()) ns = s_ov;
     p.nsplit = (int)ns;
