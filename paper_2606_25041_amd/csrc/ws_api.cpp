@@ -125,7 +125,7 @@ struct StepPlan {
 
 // Query tile and KV split count of a streaming step.
 // One launch shape: 8 waves x 32 query rows (256-query tiles).
-ws::TileShape default_shape() { return ws::TileShape{1, 8}; }
+ws::TileShape default_shape() { return ws::TileShape{1, 8, 1}; }
 
 // Per-item fixed cost (prologue, epilogue, partial stores) in units of one
 // 64-key tile of the loop, for the split model below.
@@ -235,6 +235,33 @@ int dispatch_time(int cus, const ItemGroup *groups, int ngroups) {
         }
     }
     return q[len - 1].at;
+}
+
+// rounds of work-groups up to which their order is the launch's time
+constexpr int64_t FEW_ROUNDS = 6;
+
+// Query tile of a prefill: 256 rows, or 128 rows whose keys the work-group's
+// two halves share (items half as long, twice as many), where few items leave
+// compute units idle or the longest sets the time.  Modelled as a longest-first
+// dispatch of the causal items on one XCD's compute units, in 64-key tiles
+// (~1.75 us): a 256-row item i takes 4 (i + 1) and a fixed 2.5, a 128-row item
+// half its 2 (i + 1) tiles at 1.12 (each step loads two) and a fixed 3.5 (the
+// halves are merged); it has to win 7 % (GQA 32/8, 1.1k tokens 40.4 -> 31.8
+// us; 8 heads of 64, 1.8k tokens 35.8 -> 21.1; at 3.3k tokens GQA 40/8 the two
+// are equal and the 256-row tile stays).
+ws::TileShape plan_prefill(int num_cus, int batch, int hq, int seq) {
+    constexpr int MAX = 64, ONE = 100;   // sizes in hundredths
+    ws::TileShape s = default_shape();
+    const int n1 = (seq + 255) / 256, n2 = (seq + 127) / 128;
+    const int cus = num_cus / ws::NUM_XCD;
+    const int64_t per = ((int64_t)batch * hq + ws::NUM_XCD - 1) / ws::NUM_XCD;   // items of a tile level per XCD
+    if (cus < 1 || n2 > MAX || per * n1 > FEW_ROUNDS * (int64_t)cus) return s;
+    ItemGroup g1[MAX], g2[MAX];
+    for (int i = 0; i < n1; ++i) g1[i] = {4 * (n1 - i) * ONE + 250, (int)per};
+    for (int i = 0; i < n2; ++i) g2[i] = {(n2 - i) * 112 + 350, (int)per};
+    g1[0].size = (seq + 63) / 64 * ONE + 250;   // the last tile may be short
+    if (100 * (int64_t)dispatch_time(cus, g2, n2) < 93 * (int64_t)dispatch_time(cus, g1, n1)) s.kg = 2;
+    return s;
 }
 
 // Splits of a step over streams whose key counts or block lengths differ.
@@ -352,8 +379,6 @@ size_t step_workspace(const StepPlan &p, int batch, int hq, int hkv, int lq) {
     const size_t rows = ((size_t)(hq / hkv) * lq + 31) / 32 * 32;
     return (size_t)p.nsplit * batch * hkv * rows * (WS_MAX_HEAD_DIM + 2) * sizeof(float);
 }
-
-ws::TileShape plan_prefill(int) { return default_shape(); }
 
 // Backward workspace: lse * log2 e and -<dO, O> of every row (f32), then the
 // key end of each token (int32), at a 256-byte aligned offset.
@@ -973,7 +998,9 @@ int prefill_impl(ws_tensor4 q, ws_tensor4 k, ws_tensor4 v, const ws_paged_kv *kv
             if (int rc = check_pages(kv_or_null, b, seq_len)) return rc;
     }
 
-    const ws::TileShape shape = plan_prefill(seq_len);
+    int cus = 0;
+    if (ws::current_device_cus(&cus)) cus = 0;   // (the launch reports it)
+    ws::TileShape shape = plan_prefill(cus, batch, num_q_heads, seq_len);
     ws::AttnArgs a{};
     a.q = (const uint16_t *)q.ptr; a.q_sb = q.stride_b; a.q_st = q.stride_t; a.q_sh = q.stride_h;
     if (paged) {
@@ -1001,6 +1028,20 @@ int prefill_impl(ws_tensor4 q, ws_tensor4 k, ws_tensor4 v, const ws_paged_kv *kv
     a.nqt = (seq_len + shape.qtile() - 1) / shape.qtile();
     a.scale_log2 = scale * 1.4426950408889634f;
     if (!finish_work(a)) return fail(WS_ERR_SHAPE, "too many work items");
+    // Launch order.  An XCD's contiguous range of items cut through a group
+    // whenever the (stream, KV head) groups are no multiple of 8, giving one
+    // XCD the group's heavy query tiles and the next the light ones; dealt
+    // classes share them evenly (GQA 64/4, one stream of 16384: 4.94 -> 3.69
+    // ms; 12/4, 14k paged: 719 -> 549 us).  Whole groups one after another
+    // stay the order of long launches, whose groups' keys then share an L2.
+    if (cus > 0 && (a.n_work <= FEW_ROUNDS * cus || (int64_t)batch * num_kv_heads % ws::NUM_XCD)) {
+        int deal = 0;   // the fewest classes that give every XCD whole ones
+        while (((int64_t)batch * num_kv_heads << deal) % ws::NUM_XCD) ++deal;
+        a.deal_log2 = deal;
+        a.units = (int32_t)(((int64_t)batch * num_kv_heads << deal) / ws::NUM_XCD);
+        a.fd_units = ws::fastdiv_make((uint32_t)a.units);
+        a.per_xcd = a.units * ((a.per_group + (1 << deal) - 1) >> deal);
+    }
     if (int e = ws::launch_attention(a, nullptr, head_dim, shape, stream))
         return fail(WS_ERR_HIP, "prefill launch failed (hip error %d)", e);
     return ok();

@@ -98,6 +98,10 @@ struct AttnArgs {
     int32_t per_xcd;     // ceil(n_work / 8)
     int32_t per_group;   // gi * nqt * nsplit: work items per (b, KV head)
     int32_t per_qt;      // gi * nsplit: work items per (b, KV head, q-tile)
+    // prefill of few rounds: classes of items per XCD (0: groups one after
+    // another), and the classes a group's items are dealt to
+    int32_t units, deal_log2;
+    FastDiv fd_units;
     // dividers by per_group, per_qt, G, Hkv and nsplit
     FastDiv fd_group, fd_qt, fd_g, fd_hkv, fd_split;
     FastDiv fd_gq;       // divider by G (packed row -> token)
@@ -199,7 +203,8 @@ struct BwdArgs {
 struct TileShape {
     int nb;  // 32-query column blocks per wave
     int nw;  // waves per work-group
-    int qtile() const { return nb * nw * 32; }
+    int kg;  // key groups the waves are divided into (2: prefill only)
+    int qtile() const { return nb * nw * 32 / kg; }
     // work-groups resident per CU (LDS and registers allow one)
     int groups_per_cu() const { return 1; }
 };

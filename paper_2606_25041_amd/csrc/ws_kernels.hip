@@ -87,12 +87,19 @@ struct NoPlan {};
 template <bool RAGGED>
 using Plan = std::conditional_t<RAGGED, RaggedPlan, NoPlan>;
 
-template <int D, int NW, int NB, int KIND, bool F32>
+//
+// KG = 2 (prefill): the work-group takes 128 query rows, and its two halves of
+// four waves the even and the odd key tiles of the same rows, merged through
+// LDS at the end.  Twice the work items, each half as long, for the same
+// matrix work, at twice the tile loads per query row: for sequences whose
+// 256-row items leave compute units idle.
+template <int D, int NW, int NB, int KIND, bool F32, int KG>
 __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const Plan<KIND == STEP_RAGGED> rp) {
     constexpr bool step = KIND == STEP || KIND == STEP_RAGGED;
     constexpr bool RAGGED = KIND == STEP_RAGGED;
     constexpr int NT = NW * 64;
-    constexpr int QT = NW * 32 * NB;       // query rows per work-group
+    constexpr int QT = NW * 32 * NB / KG;  // query rows per work-group
+    static_assert(KG == 1 || (KG == 2 && !step), "key groups: prefill only");
     constexpr int ROWB = 2 * D;            // bytes of one key row
     constexpr int TILEB = KT * ROWB;       // bytes of one K (or V) tile
     constexpr int RPW = 1024 / ROWB;       // key rows per wave-wide 16-byte load
@@ -132,10 +139,24 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
         for (int i = 0; i < 3; ++i) pos[i] = ((const i32x4 *)&rp.pos[threadIdx.x & 31])[i];
         asm volatile("" : "+v"(pos[0]), "+v"(pos[1]), "+v"(pos[2]));
     }
-    const uint32_t w = (bid % NUM_XCD) * per_xcd + bid / NUM_XCD;
-    if (w >= n_work) return;
-    const uint32_t group = fastdiv(w, fd_group);
-    uint32_t idx = w - group * per_group;
+    // Work-group i runs on XCD i mod 8, which takes the contiguous items
+    // [x, x + 1) * per_xcd: whole KV groups, so that an XCD's work-groups share
+    // their keys in its L2.  A prefill of few rounds (units > 0) takes the
+    // groups' items dealt to `deal` classes and the classes of an XCD in turn,
+    // so that its longest items start first and every XCD has its share.
+    uint32_t group, idx;
+    if (!step && a.units > 0) {
+        const uint32_t j = bid / NUM_XCD, pos = fastdiv(j, a.fd_units);
+        const uint32_t unit = (bid % NUM_XCD) * (uint32_t)a.units + (j - pos * (uint32_t)a.units);
+        group = unit >> a.deal_log2;
+        idx = (pos << a.deal_log2) + (unit & ((1u << a.deal_log2) - 1));
+        if (idx >= per_group) return;
+    } else {
+        const uint32_t w = (bid % NUM_XCD) * per_xcd + bid / NUM_XCD;
+        if (w >= n_work) return;
+        group = fastdiv(w, fd_group);
+        idx = w - group * per_group;
+    }
     uint32_t qi, split;
     int b, kvh, hh = 0, ppos = 0;
     auto field = [&](int i) -> int { return __builtin_amdgcn_readlane(pos[i >> 2][i & 3], ppos); };
@@ -183,7 +204,8 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
     // 32-row block of the tile this wave computes: the trailing waves (which
     // issue no tile loads) take the first blocks, so a small block's rows go
     // to waves without load duty
-    const int rblk = (wave + NW / 2) % NW;
+    const int rblk = KG == 2 ? wave % (NW / 2) : (wave + NW / 2) % NW;
+    const int kg = KG == 2 ? wave / (NW / 2) : 0;   // key group: tiles t_begin + kg, + 2, ...
 
     // A step tile whose first token lies past its stream's new block (blocks
     // of different lengths, padded) holds no real row: it computes nothing
@@ -291,7 +313,8 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
     // lch = slot ^ swz(row).  The swizzle depends on the row modulo 16 only,
     // so lch is the same for all i.
     static_assert((NWD * RPW) % 16 == 0, "the swizzle must repeat across a wave's loads");
-    const int lrow0 = wave * RPW + lane / LPR;
+    const int lwave = KG == 2 ? wave % NWD : wave;   // (two key groups: either half loads)
+    const int lrow0 = lwave * RPW + lane / LPR;
     const int lch = (lane % LPR) ^ swz<D>(lrow0);
     const char *kpool_b = (const char *)a.kpool;
     const char *vpool_b = (const char *)a.vpool;
@@ -320,7 +343,7 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
     auto plan_tile = [&](int u, int s, int page) -> TileLoad {
         const int kt = u * KT;
         TileLoad t;
-        t.kd = lds_addr(smem) + s * TILEB + wave * 1024;
+        t.kd = lds_addr(smem) + s * TILEB + lwave * 1024;
         t.vd = t.kd + VRING;
         t.straddle = false;
         if (KIND != PREFILL_CONTIGUOUS && kt + KT <= n_pool) {
@@ -332,7 +355,7 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
             t.ok = t.ov = lofs_p;
         } else if (KIND != PREFILL_PAGED && kt >= n_pool && kt + KT <= k_hi) {
             // whole tile in the contiguous keys
-            const int64_t j0 = kt - n_pool + wave * RPW;
+            const int64_t j0 = kt - n_pool + lwave * RPW;
             t.bk = kc_b + j0 * kst2;
             t.bv = vc_b + j0 * vst2;
             t.sk = NWD * RPW * kst2;
@@ -351,7 +374,7 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
     // rows past the end repeat the last key (their scores are masked)
     auto issue_straddle = [&](int u, int s, int page) {
         const int kt = u * KT;
-        const uint32_t kd = lds_addr(smem) + s * TILEB + wave * 1024;
+        const uint32_t kd = lds_addr(smem) + s * TILEB + lwave * 1024;
         const uint32_t vd = kd + VRING;
         const int64_t tb = ((int64_t)page * a.Hkv + kvh) * TILEB;
         const char *kg = kpool_b + tb, *vg = vpool_b + tb;
@@ -621,7 +644,9 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
     bf16x8 pf[NB][4];
     const int n_tiles = t_end - t_begin;
     auto stage_off = [&](int t) -> uint32_t { return (uint32_t)((t - t_begin) % NSTAGE) * TILEB; };
-    if (n_tiles > 0) {
+    if constexpr (KG == 2) {
+        // (below)
+    } else if (n_tiles > 0) {
         // Prologue: the leading waves issue the first three tiles and wait
         // for the first and their query rows (the other two stay in flight
         // into loop step t_begin, as in the steady state); the trailing
@@ -670,6 +695,86 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
         if (lead) wg_barrier();
     } else {
         wait_vm_lgkm<0>();   // (the query loads)
+    }
+
+    // Two key groups.  Phase p (between two barriers) is the leading waves'
+    // MFMA block of step p / 2 (p even) or the trailing waves' (p odd), while
+    // the others run their softmax: K of tile t_begin + p is read in phase p
+    // and V of it in phase p + 2.  In its softmax phase each half issues the
+    // tile three past its own, into the stage whose V was read one phase
+    // before, and waits for it after its next MFMA block, one phase before
+    // it is read.
+    if constexpr (KG == 2) {
+        if (n_tiles > 0) {
+            int pg_next = page_glb(t_begin + kg + 3);   // page of the tile issued next
+            if (kg == 0) {
+                const int pg0 = page_glb(t_begin), pg2 = page_glb(t_begin + 2);
+                issue_tile(t_begin, 0, pg0);
+                if (n_tiles > 2) issue_tile(t_begin + 2, 2, pg2);
+                wait_tiles(n_tiles > 2 ? 1 : 0);
+            } else {
+                const int pg1 = page_glb(t_begin + 1);
+                if (n_tiles > 1) issue_tile(t_begin + 1, 1, pg1);
+                wait_vm_lgkm<0>();
+            }
+            read_q();
+            wait_vm_lgkm<63>();
+            wg_barrier();
+            if (!lead) wg_barrier();
+            const int nj = (n_tiles + 1) / 2;
+            for (int j = 0; j <= nj; ++j) {
+                asm volatile("" : "+v"(kbase), "+v"(vbase[0]), "+v"(vbase[1]), "+v"(lofs_p), "+v"(lofs_k), "+v"(lofs_v));
+                const int t = t_begin + 2 * j + kg;
+                if (busy) {
+                    if (t < t_end) qk(stage_off(t), S);
+                    if (j > 0 && t - 2 < t_end) pv(stage_off(t - 2), pf);
+                }
+                wait_vm_lgkm<0>();   // the tile issued in the last softmax phase landed
+                wg_barrier();
+                if (t + 3 < t_end) issue_tile(t + 3, (t + 3 - t_begin) % NSTAGE, pg_next);
+                if (busy && t < t_end) softmax(t, S, pf);
+                if (t + 5 < t_end) pg_next = page_glb(t + 5);
+                wait_vm_lgkm<63>();
+                wg_barrier();
+            }
+            if (lead) wg_barrier();
+        } else {
+            wait_vm_lgkm<0>();   // (the query loads)
+            wg_barrier();
+        }
+        // The odd tiles' sums go to the leading wave of the same rows, in
+        // register order; every tile and query read is behind the last barrier.
+        char *xch = smem + VRING + rblk * (32 * D * 4 + 512);
+        if (kg == 1) {
+#pragma unroll
+            for (int md = 0; md < MD; ++md)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    f32x4 val;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) val[e] = o[0][md][4 * g + e];
+                    *(f32x4 *)(xch + ((md * 4 + g) * 64 + lane) * 16) = val;
+                }
+            *(float *)(xch + 32 * D * 4 + 4 * lane) = m[0];
+            *(float *)(xch + 32 * D * 4 + 256 + 4 * lane) = l[0];
+        }
+        wait_vm_lgkm<0>();
+        wg_barrier();
+        if (kg == 1) return;
+        // rows that saw no key of a half have m = -inf there: weight 0
+        const float m1 = *(const float *)(xch + 32 * D * 4 + 4 * lane), l1 = *(const float *)(xch + 32 * D * 4 + 256 + 4 * lane);
+        const float mm = fmaxf(m[0], m1);
+        const float a0 = m[0] == -INFINITY ? 0.f : fast_exp2(m[0] - mm), a1 = m1 == -INFINITY ? 0.f : fast_exp2(m1 - mm);
+        m[0] = mm;
+        l[0] = l[0] * a0 + l1 * a1;
+#pragma unroll
+        for (int md = 0; md < MD; ++md)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 val = *(const f32x4 *)(xch + ((md * 4 + g) * 64 + lane) * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[0][md][4 * g + e] = o[0][md][4 * g + e] * a0 + val[e] * a1;
+            }
     }
 
     // ---- epilogue -----------------------------------------------------------
@@ -983,22 +1088,27 @@ __global__ __launch_bounds__(256) void append_kernel(const AppendArgs a) {
     }
 }
 
-template <int D, int KIND>
+template <int D, int KIND, int KG>
 int launch_attn_t(const AttnArgs &a, const Plan<KIND == STEP_RAGGED> &rp, hipStream_t st) {
     const dim3 grid(a.per_xcd * NUM_XCD), block(8 * 64);
     if (a.out_f32)
-        hipLaunchKernelGGL((attn_kernel<D, 8, 1, KIND, true>), grid, block, 0, st, a, rp);
+        hipLaunchKernelGGL((attn_kernel<D, 8, 1, KIND, true, KG>), grid, block, 0, st, a, rp);
     else
-        hipLaunchKernelGGL((attn_kernel<D, 8, 1, KIND, false>), grid, block, 0, st, a, rp);
+        hipLaunchKernelGGL((attn_kernel<D, 8, 1, KIND, false, KG>), grid, block, 0, st, a, rp);
     return (int)hipGetLastError();
 }
 
+template <int D, int KIND>
+int launch_prefill_t(const AttnArgs &a, int key_groups, hipStream_t st) {
+    return key_groups == 2 ? launch_attn_t<D, KIND, 2>(a, NoPlan{}, st) : launch_attn_t<D, KIND, 1>(a, NoPlan{}, st);
+}
+
 template <int D>
-int launch_attn_d(const AttnArgs &a, const RaggedPlan *rag, hipStream_t st) {
-    return rag ? launch_attn_t<D, STEP_RAGGED>(a, *rag, st)
-         : a.mode == MODE_STEP ? launch_attn_t<D, STEP>(a, NoPlan{}, st)
-         : a.paged ? launch_attn_t<D, PREFILL_PAGED>(a, NoPlan{}, st)
-                   : launch_attn_t<D, PREFILL_CONTIGUOUS>(a, NoPlan{}, st);
+int launch_attn_d(const AttnArgs &a, const RaggedPlan *rag, int key_groups, hipStream_t st) {
+    return rag ? launch_attn_t<D, STEP_RAGGED, 1>(a, *rag, st)
+         : a.mode == MODE_STEP ? launch_attn_t<D, STEP, 1>(a, NoPlan{}, st)
+         : a.paged ? launch_prefill_t<D, PREFILL_PAGED>(a, key_groups, st)
+                   : launch_prefill_t<D, PREFILL_CONTIGUOUS>(a, key_groups, st);
 }
 
 template <int D, bool VL, bool RAGGED>
@@ -1032,8 +1142,8 @@ int launch_combine_d(const AttnArgs &a, const RaggedPlan *rag, hipStream_t st) {
 int launch_attention(const AttnArgs &a, const RaggedPlan *rag, int head_dim, TileShape shape, void *stream) {
     hipStream_t st = (hipStream_t)stream;
     if (shape.nw != 8 || shape.nb != 1) return (int)hipErrorInvalidValue;
-    if (head_dim == 128) return launch_attn_d<128>(a, rag, st);
-    if (head_dim == 64) return launch_attn_d<64>(a, rag, st);
+    if (head_dim == 128) return launch_attn_d<128>(a, rag, shape.kg, st);
+    if (head_dim == 64) return launch_attn_d<64>(a, rag, shape.kg, st);
     return (int)hipErrorInvalidValue;
 }
 
