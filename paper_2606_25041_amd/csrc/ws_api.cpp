@@ -908,6 +908,7 @@ int step_impl(ws_tensor4 q, ws_tensor4 k_new, ws_tensor4 v_new, const ws_paged_k
     a.gi = 1;
     a.nrows = a.G * new_len;
     a.nrb = (a.nrows + 31) / 32;
+    a.fd_nrb = ws::fastdiv_make((uint32_t)a.nrb);
     if (plan.nsplit > 1) {
         a.part_o = (float *)workspace;
         a.part_ml = a.part_o + (size_t)plan.nsplit * batch * a.Hkv * a.nrb * 32 * kv->head_dim;

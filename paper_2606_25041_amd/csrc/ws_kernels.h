@@ -114,6 +114,7 @@ struct AttnArgs {
     int32_t lens_arg[32];
     int32_t text_arg[32];   // step: segment starts by value (new_len: none)
     int32_t nl_arg[32];     // step: new-block lengths by value
+    FastDiv fd_nrb;         // divider by nrb (the merge)
 };
 
 constexpr int LENS_IN_ARGS = 32;

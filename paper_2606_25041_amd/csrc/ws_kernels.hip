@@ -908,34 +908,45 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
         append_share<D, NT>(a, b, kvh, (int)(qi * nsplit + split), napp, n_pool, nl, ptab, tid);
 }
 
+// The merge is bound by latency: one round trip of loads behind the work
+// item's decode, on work-groups that hardly fill the chip (256-token block, 24
+// heads, 10 splits: 19 MB in 6 us).  A work-group is therefore a part of one
+// 32-row block, so that the decode is a few scalar multiplications by the
+// host's dividers; 64-bit divisions per thread stood before the first load
+// (6.3 -> 5.8 us with the 16-byte stores and the 12-split loop; the step 26.0
+// -> 25.5 us, solver loop of 8 steps 211.0 -> 208.0 us).  Threads of a
+// work-group: bf16 128 (decode of 24 packed rows over four streams 45.2 us
+// against 45.6 with 256, the step 26.1 against 26.3), f32 256 (six streams of
+// 148 rows, head dim 64: 16.5 us against 17.2 with 128, 16.9 before).
+template <bool F32>
+constexpr int COMBINE_NT = F32 ? 256 : 128;
+
 // bf16 output: split s holds o_s / l_s (bf16) and lse_s = m_s + log2(l_s);
 //   M = max_s lse_s,  L = sum_s 2^(lse_s - M),  o = sum_s 2^(lse_s - M) o_s / L.
 // A thread owns the 8 elements (two accumulator groups) one writer lane
 // stored with one 16-byte store, for every split.
 // VARLEN: blocks of different lengths; padding rows are skipped (their
 // partials may not exist).  SMAX >= nsplit: the split loops are unrolled
-// SMAX times (the launch takes the smallest of 8, 16, 32, which also keeps
-// the register count, and with it the waves per SIMD that hide the loads'
-// latency, down).
+// SMAX times (the launch takes the smallest of 4, 8, 12, 16, 32).
 // RAGGED: the streams have their own split counts and slots (rp); a stream
 // with one split was written by the attention launch.
 template <int D, bool VARLEN, bool RAGGED, int SMAX>
-__global__ __launch_bounds__(256) void combine16_kernel(const AttnArgs a, const Plan<RAGGED> rp) {
+__global__ __launch_bounds__(COMBINE_NT<false>) void combine16_kernel(const AttnArgs a, const Plan<RAGGED> rp) {
     static_assert(SMAX <= MAX_SPLITS, "at most MAX_SPLITS partials");
     constexpr int MD = D / 32;
     constexpr int PER_BLK = 2 * MD * 64;      // 16-byte items per 32-row block
-    const int64_t nblk = (int64_t)a.B * a.Hkv * a.nrb;
-    const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (u >= nblk * PER_BLK) return;
-    const int64_t blk = u / PER_BLK;
-    const int item = (int)(u % PER_BLK);
+    constexpr int NT = COMBINE_NT<false>;
+    static_assert(PER_BLK % NT == 0, "a work-group stays within one block");
+    const uint32_t blk = blockIdx.x / (PER_BLK / NT);
+    const int item = (int)(blockIdx.x % (PER_BLK / NT) * NT + threadIdx.x);
     const int lane = item & 63;
     const int pg = item >> 6;                 // md * 2 + g0 / 2
-    const int r = (int)(blk % a.nrb) * 32 + (lane & 31);   // packed row
+    const uint32_t grp = fastdiv(blk, a.fd_nrb);
+    const int r = (int)(blk - grp * (uint32_t)a.nrb) * 32 + (lane & 31);   // packed row
     if (r >= a.nrows) return;
-    const int kvh = (int)((blk / a.nrb) % a.Hkv);
-    const int b = (int)(blk / ((int64_t)a.nrb * a.Hkv));
-    const int t = r / a.G;
+    const int b = (int)fastdiv(grp, a.fd_hkv);
+    const int kvh = (int)(grp - (uint32_t)b * (uint32_t)a.Hkv);
+    const int t = (int)fastdiv((uint32_t)r, a.fd_gq);
     if (VARLEN && t >= a.new_lens[b]) return;   // padding row: left unwritten
     const int hq = kvh * a.G + (r - t * a.G);
     int S = a.nsplit, slot = b * S;
@@ -945,7 +956,7 @@ __global__ __launch_bounds__(256) void combine16_kernel(const AttnArgs a, const 
         if (S == 1) return;
     }
     const int64_t sb = (int64_t)a.Hkv * a.nrb;   // blocks per slot
-    const int64_t pb = slot * sb + (blk - b * sb);
+    const int64_t pb = slot * sb + (int64_t)(blk - (uint32_t)b * (uint32_t)sb);
     const float *pl = a.part_ml + pb * 32 + (lane & 31);
     const uint16_t *po = (const uint16_t *)a.part_o + pb * (32 * D) + pg * 512 + 8 * lane;
     const int64_t ls = sb * 32;               // split stride of lse
@@ -980,15 +991,17 @@ __global__ __launch_bounds__(256) void combine16_kernel(const AttnArgs a, const 
         }
     }
     const float inv = L > 0.f ? 1.f / L : 0.f;
-    const int md = pg >> 1, g0 = 2 * (pg & 1), hf = lane >> 5;
-    uint16_t *op = (uint16_t *)a.out + b * a.o_sb + (int64_t)t * a.o_st + hq * a.o_sh + 32 * md + 4 * hf;
+    // the halves of the wave hold 4 elements each of two 8-element groups of
+    // a row; after the swap each holds one group whole: one 16-byte store
+    u32x4 val;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        u32x2 val;
-        val[0] = pack_bf16x2(acc[4 * h + 0] * inv, acc[4 * h + 1] * inv);
-        val[1] = pack_bf16x2(acc[4 * h + 2] * inv, acc[4 * h + 3] * inv);
-        *(u32x2 *)(op + 8 * (g0 + h)) = val;
+        const u32x2 x = __builtin_amdgcn_permlane32_swap(pack_bf16x2(acc[2 * h] * inv, acc[2 * h + 1] * inv),
+                                                         pack_bf16x2(acc[4 + 2 * h] * inv, acc[5 + 2 * h] * inv), false, false);
+        val[h] = x[0];
+        val[2 + h] = x[1];
     }
+    *(u32x4 *)((uint16_t *)a.out + b * a.o_sb + (int64_t)t * a.o_st + hq * a.o_sh + 16 * pg + 8 * (lane >> 5)) = val;
     if (a.lse && pg == 0 && lane < 32)
         a.lse[((int64_t)b * a.Hq + hq) * a.Lq + t] = (M + __builtin_amdgcn_logf(L)) * 0.69314718055994531f;
 }
@@ -1003,21 +1016,21 @@ __global__ __launch_bounds__(256) void combine16_kernel(const AttnArgs a, const 
 // together: 20 splits of 240 blocks, head dim 64: 11.3 us as a rolled loop
 // over the splits.
 template <int D, bool VARLEN, bool RAGGED, int SMAX>
-__global__ __launch_bounds__(256) void combine_kernel(const AttnArgs a, const Plan<RAGGED> rp) {
+__global__ __launch_bounds__(COMBINE_NT<true>) void combine_kernel(const AttnArgs a, const Plan<RAGGED> rp) {
     constexpr int MD = D / 32;
     constexpr int PER_BLK = MD * 4 * 64;      // float4 items per 32-row block
-    const int64_t nblk = (int64_t)a.B * a.Hkv * a.nrb;
-    const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (u >= nblk * PER_BLK) return;
-    const int64_t blk = u / PER_BLK;
-    const int item = (int)(u % PER_BLK);
+    constexpr int NT = COMBINE_NT<true>;
+    static_assert(PER_BLK % NT == 0, "a work-group stays within one block");
+    const uint32_t blk = blockIdx.x / (PER_BLK / NT);
+    const int item = (int)(blockIdx.x % (PER_BLK / NT) * NT + threadIdx.x);
     const int lane = item & 63;
     const int mg = item >> 6;                 // md * 4 + g
-    const int r = (int)(blk % a.nrb) * 32 + (lane & 31);   // packed row
+    const uint32_t grp = fastdiv(blk, a.fd_nrb);
+    const int r = (int)(blk - grp * (uint32_t)a.nrb) * 32 + (lane & 31);   // packed row
     if (r >= a.nrows) return;
-    const int kvh = (int)((blk / a.nrb) % a.Hkv);
-    const int b = (int)(blk / ((int64_t)a.nrb * a.Hkv));
-    const int t = r / a.G;
+    const int b = (int)fastdiv(grp, a.fd_hkv);
+    const int kvh = (int)(grp - (uint32_t)b * (uint32_t)a.Hkv);
+    const int t = (int)fastdiv((uint32_t)r, a.fd_gq);
     if (VARLEN && t >= a.new_lens[b]) return;   // padding row: left unwritten
     const int hq = kvh * a.G + (r - t * a.G);
     const int d0 = 32 * (mg >> 2) + 8 * (mg & 3) + 4 * (lane >> 5);
@@ -1028,7 +1041,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const AttnArgs a, const Pl
         if (S == 1) return;
     }
     const int64_t sb = (int64_t)a.Hkv * a.nrb;   // blocks per slot
-    const int64_t pb = slot * sb + (blk - b * sb);
+    const int64_t pb = slot * sb + (int64_t)(blk - (uint32_t)b * (uint32_t)sb);
     const float2 *ml = (const float2 *)a.part_ml + pb * 32 + (lane & 31);
     const float *po = a.part_o + pb * (32 * D) + (int64_t)mg * 256 + 4 * lane;
     const int64_t mls = sb * 32;              // split stride of (m, l)
@@ -1113,16 +1126,19 @@ int launch_attn_d(const AttnArgs &a, const RaggedPlan *rag, int key_groups, hipS
 
 template <int D, bool VL, bool RAGGED>
 int launch_combine_t(const AttnArgs &a, const Plan<RAGGED> &rp, int nsplit, hipStream_t st) {
-    const int64_t per_blk = (int64_t)(D / 32) * (a.out_f32 ? 4 : 2) * 64;   // items per 32-row block
-    const dim3 grid((unsigned)(((int64_t)a.B * a.Hkv * a.nrb * per_blk + 255) / 256));
+    const int per_blk = D / 32 * (a.out_f32 ? 4 : 2) * 64;   // items per 32-row block
+    const int nt = a.out_f32 ? COMBINE_NT<true> : COMBINE_NT<false>;
+    const dim3 grid((unsigned)((int64_t)a.B * a.Hkv * a.nrb * (per_blk / nt)));
     auto launch = [&](auto smax) {
         constexpr int SMAX = decltype(smax)::value;
         if (a.out_f32)
-            hipLaunchKernelGGL((combine_kernel<D, VL, RAGGED, SMAX>), grid, dim3(256), 0, st, a, rp);
+            hipLaunchKernelGGL((combine_kernel<D, VL, RAGGED, SMAX>), grid, dim3(nt), 0, st, a, rp);
         else
-            hipLaunchKernelGGL((combine16_kernel<D, VL, RAGGED, SMAX>), grid, dim3(256), 0, st, a, rp);
+            hipLaunchKernelGGL((combine16_kernel<D, VL, RAGGED, SMAX>), grid, dim3(nt), 0, st, a, rp);
     };
-    if (nsplit <= 8) launch(std::integral_constant<int, 8>{});
+    if (nsplit <= 4) launch(std::integral_constant<int, 4>{});
+    else if (nsplit <= 8) launch(std::integral_constant<int, 8>{});
+    else if (nsplit <= 12) launch(std::integral_constant<int, 12>{});
     else if (nsplit <= 16) launch(std::integral_constant<int, 16>{});
     else launch(std::integral_constant<int, MAX_SPLITS>{});
     return (int)hipGetLastError();
