@@ -264,6 +264,21 @@ ws::TileShape plan_prefill(int num_cus, int batch, int hq, int seq) {
     return s;
 }
 
+// Whether a prefill's items may be dealt to 2^deal classes per group.  Classes
+// of a group that are one item short get work-groups that find no item; each
+// holds a compute unit for about two key tiles.  They cost nothing while the
+// launch fits one round; past that they may take 5 % of the items' own tiles
+// (501 sequences of 160 tokens, one head, dealt: eight work-groups per item,
+// 71.6 us against 22.6 in plain order).  Launches near the grid's limit (2^32
+// threads) keep the plain order, which has no such work-groups.
+bool deal_pays(int cus, const ws::AttnArgs &a, int64_t groups, int deal, ws::TileShape shape) {
+    const int64_t items = (((int64_t)a.per_group + (1 << deal) - 1) >> deal << deal) * groups;
+    const int64_t none = items - a.n_work;
+    // a causal item's mean tiles, in hundredths (as in plan_prefill)
+    const int64_t mean = shape.kg == 2 ? 56 * (a.nqt + 1) + 350 : 200 * (a.nqt + 1) + 250;
+    return items <= cus || (items <= (int64_t)1 << 22 && 20 * 200 * none <= mean * a.n_work);
+}
+
 // Splits of a step over streams whose key counts or block lengths differ.
 // One split count for all of them (plan_step) lets the longest stream set
 // the time: with caches of 32768, 9001, 2750 and 517 tokens and 8 KV heads,
@@ -1035,11 +1050,12 @@ int prefill_impl(ws_tensor4 q, ws_tensor4 k, ws_tensor4 v, const ws_paged_kv *kv
     // classes share them evenly (GQA 64/4, one stream of 16384: 4.94 -> 3.69
     // ms; 12/4, 14k paged: 719 -> 549 us).  Whole groups one after another
     // stay the order of long launches, whose groups' keys then share an L2.
-    if (cus > 0 && (a.n_work <= FEW_ROUNDS * cus || (int64_t)batch * num_kv_heads % ws::NUM_XCD)) {
-        int deal = 0;   // the fewest classes that give every XCD whole ones
-        while (((int64_t)batch * num_kv_heads << deal) % ws::NUM_XCD) ++deal;
+    const int64_t groups = (int64_t)batch * num_kv_heads;
+    int deal = 0;   // the fewest classes that give every XCD whole ones
+    while ((groups << deal) % ws::NUM_XCD) ++deal;
+    if (cus > 0 && (a.n_work <= FEW_ROUNDS * cus || deal) && deal_pays(cus, a, groups, deal, shape)) {
         a.deal_log2 = deal;
-        a.units = (int32_t)(((int64_t)batch * num_kv_heads << deal) / ws::NUM_XCD);
+        a.units = (int32_t)((groups << deal) / ws::NUM_XCD);
         a.fd_units = ws::fastdiv_make((uint32_t)a.units);
         a.per_xcd = a.units * ((a.per_group + (1 << deal) - 1) >> deal);
     }

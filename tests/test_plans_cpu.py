@@ -1,0 +1,48 @@
+"""The host's launch plans, read on the CPU (tests/plan_probe.py): what they
+launch, that every work item is launched once, and the sizes they ask for."""
+import random
+
+import pytest
+
+from tests import plan_probe
+
+MAX_GRID = ((1 << 32) - 1) // 512   # work-groups of 512 threads in one launch
+
+
+def _dealt_items(p):
+    """(group, item) of every work-group of a prefill in dealt order, as the
+    kernel decodes its block id; None where it finds no item."""
+    for j in range(p.launched // 8):
+        pos = j // p.units
+        for xcd in range(8):
+            unit = xcd * p.units + j - pos * p.units
+            idx = (pos << p.deal_log2) + (unit & ((1 << p.deal_log2) - 1))
+            yield (unit >> p.deal_log2, idx) if idx < p.per_group else None
+
+
+def test_prefill_order_launches_every_item_once():
+    rng = random.Random(3)
+    dealt = 0
+    for _ in range(300):
+        hkv, g = rng.choice((1, 1, 2, 3, 4, 5, 8)), rng.choice((1, 1, 2, 3, 5))
+        batch, seq = rng.choice((1, 2, 3, 7, 33, 120)), rng.choice((1, 64, 200, 300, 700, 1300, 2500))
+        p = plan_probe.prefill(batch, hkv * g, hkv, 64, seq)
+        assert p.status == 0
+        if p.units:
+            dealt += 1
+            got = [x for x in _dealt_items(p) if x is not None]
+            assert len(got) == len(set(got)) == p.items == batch * hkv * p.per_group
+        else:
+            assert p.items <= p.launched < p.items + 8
+    assert dealt > 50
+
+
+@pytest.mark.parametrize("batch,hq,hkv,seq", [(501, 1, 1, 160), (1001, 1, 1, 17), (67, 3, 1, 240), (333, 1, 1, 400),
+                                              (1 << 20 | 1, 1, 1, 1)])
+def test_prefill_of_small_groups_launches_its_items_only(batch, hq, hkv, seq):
+    """Many groups of few items, no multiple of 8 of them: dealt to classes,
+    most of the launch (up to 7 of 8 work-groups) held no item, and the largest
+    no longer fitted a grid."""
+    p = plan_probe.prefill(batch, hq, hkv, 64, seq)
+    assert p.status == 0 and p.launched <= MAX_GRID
+    assert p.launched <= max(256, 1.05 * p.items + 8), p
