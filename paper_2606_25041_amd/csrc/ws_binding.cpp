@@ -5,7 +5,9 @@
 // here: device tensors, (host, device) pairs of int32 arrays.  Anything else
 // (another type, a wrong shape or dtype) returns None before anything is
 // enqueued, and the Python code, which states the checks and
-// raises their errors, takes the call.
+// raises their errors, takes the call.  Python objects are read first; the
+// allocations and the C ABI call (validation, planning, launches, which block
+// on a full hardware queue) run without the GIL, as through ctypes.
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -93,10 +95,20 @@ bool int_pair(PyObject *o, std::initializer_list<int64_t> shape, bool packed, In
     return true;
 }
 
+// Runs its scope without the GIL.
+struct NoGil {
+    PyThreadState *state = PyEval_SaveThread();
+    ~NoGil() { PyEval_RestoreThread(state); }
+};
+
 PyObject *names[7];   // attribute names of PagedCache, in the order below
 
-// The paged cache's descriptor, with its table checked for `batch` rows
-bool paged(PyObject *cache, int64_t batch, ws_paged_kv &d) {
+// The paged cache's descriptor, with its table checked for `batch` rows.  The
+// cache's tensors are held: without the GIL another thread may replace them.
+struct Paged : ws_paged_kv {
+    at::Tensor hold[4];
+};
+bool paged(PyObject *cache, int64_t batch, Paged &d) {
     PyObject *v[7] = {};
     bool ok = true;
     for (int i = 0; i < 7 && ok; ++i) ok = (v[i] = PyObject_GetAttr(cache, names[i])) != nullptr;
@@ -110,11 +122,13 @@ bool paged(PyObject *cache, int64_t batch, ws_paged_kv &d) {
         ok = k && vp && th && td && th->dim() == 2 && th->size(0) >= batch && td->sizes() == th->sizes() &&
              PyLong_CheckExact(v[4]) && PyLong_CheckExact(v[5]) && PyLong_CheckExact(v[6]);
     }
-    if (ok)
-        d = ws_paged_kv{k->data_ptr(), vp->data_ptr(), (const int32_t *)td->data_ptr(), (const int32_t *)th->data_ptr(),
+    if (ok) {
+        static_cast<ws_paged_kv &>(d) = ws_paged_kv{k->data_ptr(), vp->data_ptr(), (const int32_t *)td->data_ptr(), (const int32_t *)th->data_ptr(),
                         (int32_t)PyLong_AsLong(v[4]), WS_PAGE_SIZE, (int32_t)th->size(1), (int32_t)PyLong_AsLong(v[5]),
                         (int32_t)PyLong_AsLong(v[6])};
-    for (PyObject *o : v) Py_XDECREF(o);   // (the cache keeps them alive)
+        d.hold[0] = *k, d.hold[1] = *vp, d.hold[2] = *th, d.hold[3] = *td;
+    }
+    for (PyObject *o : v) Py_XDECREF(o);
     return ok;
 }
 
@@ -131,16 +145,18 @@ bool scale_of(PyObject *o, int64_t d, float &s) {
     return true;
 }
 
-// An output of the given shape: the caller's tensor, or a new one of `type`
-bool output(PyObject *o, std::initializer_list<int64_t> shape, at::ScalarType type, const at::Tensor &like, at::Tensor &t) {
-    if (o == Py_None) {
-        t = at::empty(at::IntArrayRef(shape), like.options().dtype(type));
-        return true;
-    }
+// The caller's output of the given shape, or, for None, undefined
+bool given(PyObject *o, std::initializer_list<int64_t> shape, at::Tensor &t) {
+    if (o == Py_None) return true;
     const at::Tensor *p = tensor(o);
     if (!p || !p->is_cuda() || !shaped(*p, shape)) return false;
     t = *p;
     return true;
+}
+
+// A new output of the given shape where the caller gave none
+void allocate(at::Tensor &t, std::initializer_list<int64_t> shape, at::ScalarType type, const at::Tensor &like) {
+    if (!t.defined()) t = at::empty(at::IntArrayRef(shape), like.options().dtype(type));
 }
 
 bool flag(PyObject *o, bool &b) {
@@ -176,15 +192,19 @@ PyObject *append(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const at::Tensor *k = tensor(a[2]);
     if (!k || k->dim() != 4) Py_RETURN_NONE;
     const int64_t B = k->size(0), L = k->size(1);
-    ws_paged_kv kv;
+    Paged kv{};
     ws_tensor4 kd, vd;
     Ints lens, nl;
     if (!paged(a[0], B, kv) || !token_tensor(k, {B, L, kv.num_kv_heads, kv.head_dim}, kd) ||
         !token_tensor(tensor(a[3]), {B, L, kv.num_kv_heads, kv.head_dim}, vd) || a[1] == Py_None ||
         !int_pair(a[1], {B}, false, lens) || !int_pair(a[4], {B}, true, nl))
         Py_RETURN_NONE;
-    const int rc = nl.host ? abi.kv_append_varlen(&kv, B, lens.host, lens.dev, nl.host, nl.dev, L, kd, vd, stream())
-                           : abi.kv_append(&kv, B, lens.host, lens.dev, L, kd, vd, stream());
+    int rc;
+    {
+        NoGil free;
+        rc = nl.host ? abi.kv_append_varlen(&kv, B, lens.host, lens.dev, nl.host, nl.dev, L, kd, vd, stream())
+                     : abi.kv_append(&kv, B, lens.host, lens.dev, L, kd, vd, stream());
+    }
     return PyLong_FromLong(rc);
     END_HANDLE_TH_ERRORS
 }
@@ -199,7 +219,7 @@ PyObject *step(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!q || q->dim() != 4) Py_RETURN_NONE;
     const int64_t B = q->size(0), L = q->size(1), H = q->size(2), D = q->size(3);
     if (B == 0 || L == 0) Py_RETURN_NONE;
-    ws_paged_kv kv;
+    Paged kv{};
     ws_tensor4 qd, kd, vd, od;
     Ints lens, text, nl;
     bool fuse, want_lse, noalloc;
@@ -215,37 +235,44 @@ PyObject *step(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const at::Tensor *wsp = a[11] == Py_None ? nullptr : tensor(a[11]);
     if (a[11] != Py_None && !wsp) Py_RETURN_NONE;
     at::Tensor out, lse, own;
-    if (!output(a[7], {B, L, H, D}, type, *q, out) || !token_tensor(&out, {B, L, H, D}, od)) Py_RETURN_NONE;
-    if ((want_lse || a[10] != Py_None) && !output(a[10], {B, H, L}, at::kFloat, *q, lse)) Py_RETURN_NONE;
-    float *lp = lse.defined() ? (float *)lse.data_ptr() : nullptr;
+    const bool with_lse = want_lse || a[10] != Py_None;
+    if (!given(a[7], {B, L, H, D}, out) || (out.defined() && !token_tensor(&out, {B, L, H, D}, od)) ||
+        !given(a[10], {B, H, L}, lse))
+        Py_RETURN_NONE;
     const int flags = fuse ? WS_FUSE_APPEND : 0;
-    if (noalloc)
-        return result(abi.fwd_noalloc(qd, kd, vd, &kv, lens.host, lens.dev, B, L, H, scale, flags, od, lp, stream()),
-                      {out, lse});
-    void *wp = nullptr;
-    size_t wn = 0;
-    if (wsp) {
-        wp = wsp->data_ptr();
-        wn = wsp->numel();
-    } else {
-        int32_t most = 0;
-        for (int64_t b = 0; b < B; ++b) most = std::max(most, lens.host[b * lens.h->stride(0)]);
-        wn = nl.host ? abi.workspace_bytes_varlen(B, H, kv.num_kv_heads, L, lens.host, nl.host)
-                     : abi.workspace_bytes(WS_OP_STEP, B, H, kv.num_kv_heads, L, (int32_t)std::min<int64_t>(most + L, INT32_MAX));
-        if (wn) {
-            own = at::empty({(int64_t)wn}, q->options().dtype(at::kByte));
-            wp = own.data_ptr();
-        }
-    }
     int rc;
-    if (nl.host)
-        rc = abi.fwd_varlen(qd, kd, vd, &kv, lens.host, lens.dev, nl.host, nl.dev, text.host, text.dev, B, L, H, scale, flags,
-                            od, lp, wp, wn, stream());
-    else if (text.host)
-        rc = abi.fwd_text(qd, kd, vd, &kv, lens.host, lens.dev, text.host, text.dev, B, L, H, scale, flags, od, lp, wp, wn,
-                          stream());
-    else
-        rc = abi.fwd(qd, kd, vd, &kv, lens.host, lens.dev, B, L, H, scale, flags, od, lp, wp, wn, stream());
+    {
+        NoGil free;
+        allocate(out, {B, L, H, D}, type, *q);
+        token_tensor(&out, {B, L, H, D}, od);
+        if (with_lse) allocate(lse, {B, H, L}, at::kFloat, *q);
+        float *lp = lse.defined() ? (float *)lse.data_ptr() : nullptr;
+        void *wp = nullptr;
+        size_t wn = 0;
+        if (wsp) {
+            wp = wsp->data_ptr();
+            wn = wsp->numel();
+        } else if (!noalloc) {
+            int32_t most = 0;
+            for (int64_t b = 0; b < B; ++b) most = std::max(most, lens.host[b * lens.h->stride(0)]);
+            wn = nl.host ? abi.workspace_bytes_varlen(B, H, kv.num_kv_heads, L, lens.host, nl.host)
+                         : abi.workspace_bytes(WS_OP_STEP, B, H, kv.num_kv_heads, L, (int32_t)std::min<int64_t>(most + L, INT32_MAX));
+            if (wn) {
+                own = at::empty({(int64_t)wn}, q->options().dtype(at::kByte));
+                wp = own.data_ptr();
+            }
+        }
+        if (noalloc)
+            rc = abi.fwd_noalloc(qd, kd, vd, &kv, lens.host, lens.dev, B, L, H, scale, flags, od, lp, stream());
+        else if (nl.host)
+            rc = abi.fwd_varlen(qd, kd, vd, &kv, lens.host, lens.dev, nl.host, nl.dev, text.host, text.dev, B, L, H, scale,
+                                flags, od, lp, wp, wn, stream());
+        else if (text.host)
+            rc = abi.fwd_text(qd, kd, vd, &kv, lens.host, lens.dev, text.host, text.dev, B, L, H, scale, flags, od, lp, wp,
+                              wn, stream());
+        else
+            rc = abi.fwd(qd, kd, vd, &kv, lens.host, lens.dev, B, L, H, scale, flags, od, lp, wp, wn, stream());
+    }
     return result(rc, {out, lse});
     END_HANDLE_TH_ERRORS
 }
@@ -260,7 +287,7 @@ PyObject *prefill(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const int64_t B = q->size(0), L = q->size(1), H = q->size(2), D = q->size(3);
     const bool contiguous = a[1] != Py_None;
     if (contiguous != (a[2] != Py_None)) Py_RETURN_NONE;
-    ws_paged_kv kv{};
+    Paged kv{};
     ws_tensor4 qd, kd{nullptr, WS_DTYPE_BF16, 0, 0, 0}, vd = kd, od;
     Ints off, text;
     bool want_lse;
@@ -293,13 +320,22 @@ PyObject *prefill(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const at::ScalarType type = a[7] == Py_None ? dtype_of(a[8]) : at::kBFloat16;
     if (type != at::kBFloat16 && type != at::kFloat) Py_RETURN_NONE;
     at::Tensor out, lse;
-    if (!output(a[7], {B, L, H, D}, type, *q, out) || !token_tensor(&out, {B, L, H, D}, od)) Py_RETURN_NONE;
-    if ((want_lse || a[10] != Py_None) && !output(a[10], {B, H, L}, at::kFloat, *q, lse)) Py_RETURN_NONE;
-    float *lp = lse.defined() ? (float *)lse.data_ptr() : nullptr;
+    const bool with_lse = want_lse || a[10] != Py_None;
+    if (!given(a[7], {B, L, H, D}, out) || (out.defined() && !token_tensor(&out, {B, L, H, D}, od)) ||
+        !given(a[10], {B, H, L}, lse))
+        Py_RETURN_NONE;
     const ws_paged_kv *kvp = a[5] != Py_None ? &kv : nullptr;
-    const int rc = text.host ? abi.prefill_text(qd, kd, vd, kvp, off.host, off.dev, text.host, text.dev, B, L, nb, H, hkv, D,
-                                                scale, od, lp, stream())
-                             : abi.prefill(qd, kd, vd, kvp, off.host, off.dev, B, L, nb, H, hkv, D, scale, od, lp, stream());
+    int rc;
+    {
+        NoGil free;
+        allocate(out, {B, L, H, D}, type, *q);
+        token_tensor(&out, {B, L, H, D}, od);
+        if (with_lse) allocate(lse, {B, H, L}, at::kFloat, *q);
+        float *lp = lse.defined() ? (float *)lse.data_ptr() : nullptr;
+        rc = text.host ? abi.prefill_text(qd, kd, vd, kvp, off.host, off.dev, text.host, text.dev, B, L, nb, H, hkv, D, scale,
+                                          od, lp, stream())
+                       : abi.prefill(qd, kd, vd, kvp, off.host, off.dev, B, L, nb, H, hkv, D, scale, od, lp, stream());
+    }
     return result(rc, {out, lse});
     END_HANDLE_TH_ERRORS
 }
@@ -328,18 +364,30 @@ PyObject *prefill_bwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const at::Tensor *wsp = a[12] == Py_None ? nullptr : tensor(a[12]);
     if (a[12] != Py_None && !wsp) Py_RETURN_NONE;
     at::Tensor dq, dk, dv, own;
-    if (!output(a[9], {B, L, H, D}, at::kFloat, *q, dq) || !token_tensor(&dq, {B, L, H, D}, dqd) ||
-        !output(a[10], {B, L, hkv, D}, at::kFloat, *q, dk) || !token_tensor(&dk, {B, L, hkv, D}, dkd) ||
-        !output(a[11], {B, L, hkv, D}, at::kFloat, *q, dv) || !token_tensor(&dv, {B, L, hkv, D}, dvd))
+    if (!given(a[9], {B, L, H, D}, dq) || (dq.defined() && !token_tensor(&dq, {B, L, H, D}, dqd)) ||
+        !given(a[10], {B, L, hkv, D}, dk) || (dk.defined() && !token_tensor(&dk, {B, L, hkv, D}, dkd)) ||
+        !given(a[11], {B, L, hkv, D}, dv) || (dv.defined() && !token_tensor(&dv, {B, L, hkv, D}, dvd)))
         Py_RETURN_NONE;
-    if (!wsp) {
-        const size_t need = abi.workspace_bytes(WS_OP_PREFILL_BWD, B, H, hkv, L, L);
-        if (!need) Py_RETURN_NONE;
-        own = at::empty({(int64_t)need}, q->options().dtype(at::kByte));
-        wsp = &own;
+    int rc = -1;
+    {
+        NoGil free;
+        const size_t need = wsp ? 0 : abi.workspace_bytes(WS_OP_PREFILL_BWD, B, H, hkv, L, L);
+        if (wsp || need) {
+            allocate(dq, {B, L, H, D}, at::kFloat, *q);
+            allocate(dk, {B, L, hkv, D}, at::kFloat, *q);
+            allocate(dv, {B, L, hkv, D}, at::kFloat, *q);
+            token_tensor(&dq, {B, L, H, D}, dqd);
+            token_tensor(&dk, {B, L, hkv, D}, dkd);
+            token_tensor(&dv, {B, L, hkv, D}, dvd);
+            if (!wsp) {
+                own = at::empty({(int64_t)need}, q->options().dtype(at::kByte));
+                wsp = &own;
+            }
+            rc = abi.bwd(qd, kd, vd, od, dd, (const float *)lse->data_ptr(), off.host, off.dev, text.host, text.dev, B, L, nb,
+                         H, hkv, D, scale, dqd, dkd, dvd, wsp->data_ptr(), wsp->numel(), stream());
+        }
     }
-    const int rc = abi.bwd(qd, kd, vd, od, dd, (const float *)lse->data_ptr(), off.host, off.dev, text.host, text.dev, B, L,
-                           nb, H, hkv, D, scale, dqd, dkd, dvd, wsp->data_ptr(), wsp->numel(), stream());
+    if (rc < 0) Py_RETURN_NONE;   // (the Python code names the mistake)
     return result(rc, {dq, dk, dv});
     END_HANDLE_TH_ERRORS
 }

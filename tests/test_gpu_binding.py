@@ -1,6 +1,11 @@
 """The native marshalling against the Python (ctypes) marshalling: the same
 calls give bitwise the same results through either, whatever form the
 arguments take, and what one refuses the other refuses with the same error."""
+import ctypes
+import subprocess
+import threading
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -171,3 +176,48 @@ def test_prefill_and_gradient_forms(both, form):
         both(lambda: ws.block_causal_prefill_bwd(q, k, v[:, :, :1], out, q, lse, offsets))
         small = torch.empty(16, dtype=torch.uint8, device="cuda")
         both(lambda: ws.block_causal_prefill_bwd(q, k, v, out, q, lse, offsets, workspace=small))
+
+
+def test_calls_run_without_the_gil(tmp_path):
+    """While a call is inside the library, other Python threads run (a launch
+    may block on a full hardware queue).  The library's functions are replaced
+    by one that sleeps 0.3 s, through the native marshalling of every entry
+    point; a thread beside it that sleeps 1 ms at a time has to get on."""
+    src, so = tmp_path / "slow.c", tmp_path / "slow.so"
+    src.write_text("#include <unistd.h>\nint slow(void) { usleep(300000); return 0; }\n"
+                   "unsigned long size(void) { return 256; }\n")
+    subprocess.run(["gcc", "-O1", "-fPIC", "-shared", str(src), "-o", str(so)], check=True)
+    lib = ctypes.CDLL(str(so))
+    slow, size = (ctypes.cast(f, ctypes.c_void_p).value for f in (lib.slow, lib.size))
+    native = ws._native()
+    q, k, v = _randn(B, L, HQ, D), _randn(B, L, HKV, D, seed=3), _randn(B, L, HKV, D, seed=4)
+    cache, lens, off = _cache(B, 2, HKV, D), _pair([70, 5]), _pair([[0, L]] * B)
+    out, lse = torch.empty_like(q), torch.empty(B, HQ, L, device="cuda")
+    calls = {
+        "append": lambda: ws.kv_append(cache, lens, k, v),
+        "step": lambda: ws.block_causal_attn_fwd(q, k, v, cache, lens),
+        "noalloc": lambda: ws.block_causal_attn_fwd_noalloc(q, k, v, cache, lens, out),
+        "prefill": lambda: ws.block_causal_prefill(q, k, v, off),
+        "prefill_bwd": lambda: ws.block_causal_prefill_bwd(q, k, v, out, q, lse, off),
+    }
+    turns, stop = [0], threading.Event()
+
+    def beside():
+        while not stop.is_set():
+            time.sleep(0.001)
+            turns[0] += 1
+    thread = threading.Thread(target=beside)
+    thread.start()
+    try:
+        native.bind(*[slow] * 9, size, size)
+        for name, call in calls.items():
+            before, start = turns[0], time.perf_counter()
+            call()
+            assert time.perf_counter() - start > 0.25, (name, "did not reach the library natively")
+            assert turns[0] - before > 30, (name, turns[0] - before)
+    finally:
+        stop.set()
+        thread.join()
+        ws._bind_native(ws.library())
+    got = ws.block_causal_attn_fwd(q, k, v, cache, lens)   # the library is back
+    assert torch.isfinite(got.float()).all()
