@@ -243,13 +243,17 @@ constexpr int64_t FEW_ROUNDS = 6;
 // Query tile of a prefill: 256 rows, or 128 rows whose keys the work-group's
 // two halves share (items half as long, twice as many), where few items leave
 // compute units idle or the longest sets the time.  Modelled as a longest-first
-// dispatch of the causal items on one XCD's compute units, in 64-key tiles
-// (~1.75 us): a 256-row item i takes 4 (i + 1) and a fixed 2.5, a 128-row item
-// half its 2 (i + 1) tiles at 1.12 (each step loads two) and a fixed 3.5 (the
-// halves are merged); it has to win 7 % (GQA 32/8, 1.1k tokens 40.4 -> 31.8
-// us; 8 heads of 64, 1.8k tokens 35.8 -> 21.1; at 3.3k tokens GQA 40/8 the two
-// are equal and the 256-row tile stays).
-ws::TileShape plan_prefill(int num_cus, int batch, int hq, int seq) {
+// dispatch of the items on one XCD's compute units, in 64-key tiles (~1.75
+// us): a 256-row item takes the tiles its last row sees (mean of the streams)
+// and a fixed 2.5, a 128-row item half of its tiles at 1.12 (each step loads
+// two) and a fixed 3.5 (the halves are merged); it has to win 7 % (GQA 32/8,
+// 1.1k tokens 40.4 -> 31.8 us; 8 heads of 64, 1.8k tokens 35.8 -> 21.1; at 3.3k
+// tokens GQA 40/8 the two are equal and the 256-row tile stays).  The key ends
+// are the blocks': in one block of 1000 tokens every row sees them all, and 36
+// heads of it fill a round with 256-row items (36 us against 40 in two rounds
+// of 128-row items, which items taken as causal had promised to be shorter).
+ws::TileShape plan_prefill(int num_cus, int batch, int hq, int seq, const int32_t *offsets, const int32_t *text,
+                           int num_blocks) {
     constexpr int MAX = 64, ONE = 100;   // sizes in hundredths
     ws::TileShape s = default_shape();
     const int n1 = (seq + 255) / 256, n2 = (seq + 127) / 128;
@@ -257,9 +261,19 @@ ws::TileShape plan_prefill(int num_cus, int batch, int hq, int seq) {
     const int64_t per = ((int64_t)batch * hq + ws::NUM_XCD - 1) / ws::NUM_XCD;   // items of a tile level per XCD
     if (cus < 1 || n2 > MAX || per * n1 > FEW_ROUNDS * (int64_t)cus) return s;
     ItemGroup g1[MAX], g2[MAX];
-    for (int i = 0; i < n1; ++i) g1[i] = {4 * (n1 - i) * ONE + 250, (int)per};
-    for (int i = 0; i < n2; ++i) g2[i] = {(n2 - i) * 112 + 350, (int)per};
-    g1[0].size = (seq + 63) / 64 * ONE + 250;   // the last tile may be short
+    int64_t keys[MAX] = {};   // per 128-row tile: 64-key tiles its last row sees, over the streams
+    for (int b = 0; b < batch; ++b) {
+        const int32_t *off = offsets + (int64_t)b * (num_blocks + 1);
+        for (int i = 0, n = 0; i < n2; ++i) {
+            const int row = std::min(128 * (i + 1), seq) - 1;
+            while (off[n + 1] <= row) ++n;
+            const int end = text ? std::max(text[(int64_t)b * num_blocks + n], row + 1) : off[n + 1];
+            keys[i] += (end + 63) / 64;
+        }
+    }
+    auto tiles = [&](int i) -> int { return (int)(keys[i] * ONE / batch); };
+    for (int i = 0; i < n1; ++i) g1[i] = {tiles(std::min(2 * (n1 - i) - 1, n2 - 1)) + 250, (int)per};
+    for (int i = 0; i < n2; ++i) g2[i] = {tiles(n2 - 1 - i) * 56 / 100 + 350, (int)per};
     if (100 * (int64_t)dispatch_time(cus, g2, n2) < 93 * (int64_t)dispatch_time(cus, g1, n1)) s.kg = 2;
     return s;
 }
@@ -1016,7 +1030,7 @@ int prefill_impl(ws_tensor4 q, ws_tensor4 k, ws_tensor4 v, const ws_paged_kv *kv
 
     int cus = 0;
     if (ws::current_device_cus(&cus)) cus = 0;   // (the launch reports it)
-    ws::TileShape shape = plan_prefill(cus, batch, num_q_heads, seq_len);
+    ws::TileShape shape = plan_prefill(cus, batch, num_q_heads, seq_len, block_offsets_host, text_host, num_blocks);
     ws::AttnArgs a{};
     a.q = (const uint16_t *)q.ptr; a.q_sb = q.stride_b; a.q_st = q.stride_t; a.q_sh = q.stride_h;
     if (paged) {

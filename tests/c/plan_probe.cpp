@@ -68,14 +68,16 @@ int probe_step(int batch, int hq, int hkv, int d, int new_len, const int32_t *le
     return rc;
 }
 
-// Plans a contiguous prefill of one block per sequence.  out: key groups,
+// Plans a contiguous prefill in blocks of `block` tokens.  out: key groups,
 // units, deal_log2, per_group; work: work items, grid work-groups.
-int probe_prefill(int batch, int hq, int hkv, int d, int seq, int *out, int64_t *work) {
-    std::vector<int32_t> off((size_t)batch * 2);
-    for (int b = 0; b < batch; ++b) off[2 * b + 1] = seq;
+int probe_prefill(int batch, int hq, int hkv, int d, int seq, int block, int *out, int64_t *work) {
+    const int nb = (seq + block - 1) / block;
+    std::vector<int32_t> off;
+    for (int b = 0; b < batch; ++b)
+        for (int n = 0; n <= nb; ++n) off.push_back(std::min(n * block, seq));
     const ws_tensor4 q = tensor(WS_DTYPE_BF16, seq, hq, d), k = tensor(WS_DTYPE_BF16, seq, hkv, d);
     memset(&g_seen, 0, sizeof g_seen);
-    const int rc = ws_block_causal_prefill(q, k, k, nullptr, off.data(), (const int32_t *)g_mem, batch, seq, 1, hq, hkv, d,
+    const int rc = ws_block_causal_prefill(q, k, k, nullptr, off.data(), (const int32_t *)g_mem, batch, seq, nb, hq, hkv, d,
                                            0.1f, q, nullptr, nullptr);
     out[0] = g_seen.kg;
     out[1] = g_seen.attn.units;

@@ -41,14 +41,14 @@ def step(batch, hq, hkv, d, new_len, lens, new_lens=None, cus=256):
     return SimpleNamespace(status=rc, ragged=bool(ragged.value), splits=ns.tolist(), items=work[0], launched=work[1])
 
 
-def prefill(batch, hq, hkv, d, seq, cus=256):
-    """Status of a contiguous prefill and its plan: key groups per work-group,
+def prefill(batch, hq, hkv, d, seq, block=32, cus=256):
+    """Status of a contiguous prefill in equal blocks and its plan: key groups per work-group,
     dealt classes (units per XCD and their log2 per group, 0 units: plain
     order), items per group, work items and work-groups launched."""
     lib = _lib()
     lib.probe_cus(cus)
     out, work = (ctypes.c_int * 4)(), (ctypes.c_int64 * 2)()
-    rc = lib.probe_prefill(batch, hq, hkv, d, seq, out, work)
+    rc = lib.probe_prefill(batch, hq, hkv, d, seq, block, out, work)
     return SimpleNamespace(status=rc, key_groups=out[0], units=out[1], deal_log2=out[2], per_group=out[3],
                            items=work[0], launched=work[1])
 

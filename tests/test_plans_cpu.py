@@ -46,3 +46,18 @@ def test_prefill_of_small_groups_launches_its_items_only(batch, hq, hkv, seq):
     p = plan_probe.prefill(batch, hq, hkv, 64, seq)
     assert p.status == 0 and p.launched <= MAX_GRID
     assert p.launched <= max(256, 1.05 * p.items + 8), p
+
+
+@pytest.mark.parametrize("batch,hq,hkv,seq,block,groups", [
+    (3, 12, 4, 1000, 1000, 1),    # 144 items of 16 tiles each: one round of 256-row items, two of 128-row ones
+    (1, 24, 24, 2000, 2000, 1),
+    (1, 32, 8, 2000, 1000, 1),
+    (1, 8, 8, 1000, 1000, 2),     # both fit one round: the shorter items win
+    (3, 12, 4, 1000, 40, 2),      # nearly causal: the longest items are few
+    (1, 32, 8, 1100, 100, 2),
+    (1, 40, 8, 3300, 200, 1),
+])
+def test_prefill_tile_follows_the_blocks(batch, hq, hkv, seq, block, groups):
+    """The 128-row tile is chosen by the keys the rows really see: taken as
+    causal, long blocks looked shorter than they are."""
+    assert plan_probe.prefill(batch, hq, hkv, 128, seq, block).key_groups == groups
