@@ -914,12 +914,15 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
 // 32-row block, so that the decode is a few scalar multiplications by the
 // host's dividers; 64-bit divisions per thread stood before the first load
 // (6.3 -> 5.8 us with the 16-byte stores and the 12-split loop; the step 26.0
-// -> 25.5 us, solver loop of 8 steps 211.0 -> 208.0 us).  Threads of a
-// work-group: bf16 128 (decode of 24 packed rows over four streams 45.2 us
-// against 45.6 with 256, the step 26.1 against 26.3), f32 256 (six streams of
-// 148 rows, head dim 64: 16.5 us against 17.2 with 128, 16.9 before).
-template <bool F32>
-constexpr int COMBINE_NT = F32 ? 256 : 128;
+// -> 25.5 us, solver loop of 8 steps 211.0 -> 208.0 us).
+// Threads of a work-group (NT), bf16: 128 while such work-groups are one per
+// compute unit, which spreads the loads over twice the units (21 splits of 64
+// blocks, head dim 128: 5.0 us against 5.4; 32 of 128, head dim 64: 5.7 against
+// 6.4); past that a unit's second work-group runs after its first, and 256 are
+// faster (21 splits of 76 blocks, head dim 128: 7.1 against 5.6 us, 16 of 128:
+// 6.0 against 5.3; 18 of 160, head dim 64: 6.8 against 5.7).  f32: 256 (128
+// measured 5 to 20 % slower from 76 blocks on, a few tenths of a us faster
+// below).
 
 // bf16 output: split s holds o_s / l_s (bf16) and lse_s = m_s + log2(l_s);
 //   M = max_s lse_s,  L = sum_s 2^(lse_s - M),  o = sum_s 2^(lse_s - M) o_s / L.
@@ -930,12 +933,11 @@ constexpr int COMBINE_NT = F32 ? 256 : 128;
 // SMAX times (the launch takes the smallest of 4, 8, 12, 16, 32).
 // RAGGED: the streams have their own split counts and slots (rp); a stream
 // with one split was written by the attention launch.
-template <int D, bool VARLEN, bool RAGGED, int SMAX>
-__global__ __launch_bounds__(COMBINE_NT<false>) void combine16_kernel(const AttnArgs a, const Plan<RAGGED> rp) {
+template <int D, bool VARLEN, bool RAGGED, int SMAX, int NT>
+__global__ __launch_bounds__(NT) void combine16_kernel(const AttnArgs a, const Plan<RAGGED> rp) {
     static_assert(SMAX <= MAX_SPLITS, "at most MAX_SPLITS partials");
     constexpr int MD = D / 32;
     constexpr int PER_BLK = 2 * MD * 64;      // 16-byte items per 32-row block
-    constexpr int NT = COMBINE_NT<false>;
     static_assert(PER_BLK % NT == 0, "a work-group stays within one block");
     const uint32_t blk = blockIdx.x / (PER_BLK / NT);
     const int item = (int)(blockIdx.x % (PER_BLK / NT) * NT + threadIdx.x);
@@ -1015,11 +1017,10 @@ __global__ __launch_bounds__(COMBINE_NT<false>) void combine16_kernel(const Attn
 // are unrolled (as in combine16_kernel), so that all loads are in flight
 // together: 20 splits of 240 blocks, head dim 64: 11.3 us as a rolled loop
 // over the splits.
-template <int D, bool VARLEN, bool RAGGED, int SMAX>
-__global__ __launch_bounds__(COMBINE_NT<true>) void combine_kernel(const AttnArgs a, const Plan<RAGGED> rp) {
+template <int D, bool VARLEN, bool RAGGED, int SMAX, int NT>
+__global__ __launch_bounds__(NT) void combine_kernel(const AttnArgs a, const Plan<RAGGED> rp) {
     constexpr int MD = D / 32;
     constexpr int PER_BLK = MD * 4 * 64;      // float4 items per 32-row block
-    constexpr int NT = COMBINE_NT<true>;
     static_assert(PER_BLK % NT == 0, "a work-group stays within one block");
     const uint32_t blk = blockIdx.x / (PER_BLK / NT);
     const int item = (int)(blockIdx.x % (PER_BLK / NT) * NT + threadIdx.x);
@@ -1127,14 +1128,19 @@ int launch_attn_d(const AttnArgs &a, const RaggedPlan *rag, int key_groups, hipS
 template <int D, bool VL, bool RAGGED>
 int launch_combine_t(const AttnArgs &a, const Plan<RAGGED> &rp, int nsplit, hipStream_t st) {
     const int per_blk = D / 32 * (a.out_f32 ? 4 : 2) * 64;   // items per 32-row block
-    const int nt = a.out_f32 ? COMBINE_NT<true> : COMBINE_NT<false>;
-    const dim3 grid((unsigned)((int64_t)a.B * a.Hkv * a.nrb * (per_blk / nt)));
+    const int64_t blocks = (int64_t)a.B * a.Hkv * a.nrb;
+    int cus = 0;
+    if (int e = current_device_cus(&cus)) return e;
+    const int nt = !a.out_f32 && blocks * (per_blk / 128) <= cus ? 128 : 256;
+    const dim3 grid((unsigned)(blocks * (per_blk / nt)));
     auto launch = [&](auto smax) {
         constexpr int SMAX = decltype(smax)::value;
         if (a.out_f32)
-            hipLaunchKernelGGL((combine_kernel<D, VL, RAGGED, SMAX>), grid, dim3(nt), 0, st, a, rp);
+            hipLaunchKernelGGL((combine_kernel<D, VL, RAGGED, SMAX, 256>), grid, dim3(256), 0, st, a, rp);
+        else if (nt == 128)
+            hipLaunchKernelGGL((combine16_kernel<D, VL, RAGGED, SMAX, 128>), grid, dim3(128), 0, st, a, rp);
         else
-            hipLaunchKernelGGL((combine16_kernel<D, VL, RAGGED, SMAX>), grid, dim3(nt), 0, st, a, rp);
+            hipLaunchKernelGGL((combine16_kernel<D, VL, RAGGED, SMAX, 256>), grid, dim3(256), 0, st, a, rp);
     };
     if (nsplit <= 4) launch(std::integral_constant<int, 4>{});
     else if (nsplit <= 8) launch(std::integral_constant<int, 8>{});

@@ -37,3 +37,31 @@ def test_merge(splits, D, f32):
     assert np.abs(lse.double().cpu().numpy() - rl).max() <= gs.LSE_ABS
     out.fill_(7.0)
     assert bool((whole == 7.0).all())
+
+
+@pytest.mark.parametrize("padded", [False, True])
+@pytest.mark.parametrize("D,hkv", [(128, 4), (64, 8)])
+def test_merge_of_many_blocks(D, hkv, padded):
+    """More 32-row blocks than the merge's small work-groups are launched for
+    (one per compute unit: D / 32 of them per block), the last block ragged."""
+    B, G, Lq = (2, 3, 91) if padded else (1, 3, 175)
+    n = 3000
+    wl = inputs.step_workload("merge_many", B, G * hkv, hkv, D, Lq, [n] * B, seed=5100 + D)
+    blocks = B * hkv * -(-G * Lq // 32)
+    assert blocks * (D // 32) > torch.cuda.get_device_properties(0).multi_processor_count
+    nl = [Lq, 40] if padded else None
+    splits = ws.step_plan(B, G * hkv, hkv, Lq, wl.cache_lens, new_lens=nl)[0]
+    gs.say(f"[gpu] merge of {splits} splits, {blocks} blocks, D={D}, padded={padded}")
+    assert splits > 4
+    cache = gs.device_cache(wl, wl.cache_lens, fill_on_gpu=True)
+    q, kn, vn = (gs.to_dev_bf16(t) for t in (wl.q, wl.k_new, wl.v_new))
+    out, lse = ws.block_causal_attn_fwd(q, kn, vn, cache, wl.cache_lens, want_lse=True, new_lens=nl)
+    torch.cuda.synchronize()
+    for b in range(B):
+        sl, m = slice(b, b + 1), nl[b] if nl else Lq
+        ref, rl = oracle.step(*(inputs.bf16_bits(t[sl, :k]) for t, k in ((wl.q, m), (wl.k, n), (wl.v, n))),
+                              wl.cache_lens[sl], inputs.bf16_bits(wl.k_new[sl, :m]), inputs.bf16_bits(wl.v_new[sl, :m]),
+                              wl.scale)
+        err = np.abs(out[sl, :m].double().cpu().numpy() - ref)
+        assert err.max() <= gs.MAX_ABS and err.mean() <= gs.MEAN_ABS, (b, err.max(), err.mean())
+        assert np.abs(lse[sl, :, :m].double().cpu().numpy() - rl).max() <= gs.LSE_ABS
