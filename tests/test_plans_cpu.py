@@ -61,3 +61,14 @@ def test_prefill_tile_follows_the_blocks(batch, hq, hkv, seq, block, groups):
     """The 128-row tile is chosen by the keys the rows really see: taken as
     causal, long blocks looked shorter than they are."""
     assert plan_probe.prefill(batch, hq, hkv, 128, seq, block).key_groups == groups
+
+
+@pytest.mark.parametrize("batch,hq,hkv,new", [(24, 64, 8, 3), (32, 64, 8, 3), (32, 8, 8, 16)])
+def test_one_round_of_unsplit_streams_keeps_the_common_plan(batch, hq, hkv, new):
+    """Unsplit items that all fit one round gain nothing from another order,
+    and the per-stream kernel is slower."""
+    lens = [10 + 60 * (7 * i % batch) for i in range(batch)]
+    p = plan_probe.step(batch, hq, hkv, 128, new, lens)
+    assert p.status == 0 and not p.ragged and p.splits == [1] * batch
+    # more than a round of them is still taken longest first
+    assert plan_probe.step(batch, hq, hkv, 128, 300, lens).ragged
