@@ -366,7 +366,7 @@ bool plan_ragged(ws::RaggedPlan &r, int num_cus, const StepPlan &uni, int batch,
     // this plan 37.7 and 40.3).
     if (!room) {
         if ((int64_t)batch * hkv * uni.nqt <= (int64_t)num_cus * uni.shape.groups_per_cu()) return false;
-        if (5 * st[batch - 1].tiles * st[batch - 1].q >= 4 * st[0].tiles * st[0].q) return false;
+        if (5 * (int64_t)st[batch - 1].tiles * st[batch - 1].q >= 4 * (int64_t)st[0].tiles * st[0].q) return false;
         attempt(1);
     } else {
         attempt(0);

@@ -1,6 +1,7 @@
 """The host's launch plans, read on the CPU (tests/plan_probe.py): what they
 launch, that every work item is launched once, and the sizes they ask for."""
 import random
+import subprocess
 
 import pytest
 
@@ -72,3 +73,43 @@ def test_one_round_of_unsplit_streams_keeps_the_common_plan(batch, hq, hkv, new)
     assert p.status == 0 and not p.ragged and p.splits == [1] * batch
     # more than a round of them is still taken longest first
     assert plan_probe.step(batch, hq, hkv, 128, 300, lens).ragged
+
+
+def test_plans_of_extreme_sizes_stay_in_range(tmp_path):
+    """The host side under UBSan, over accepted sizes whose products pass 32
+    bits (2^25 key tiles, 2^22 query tiles): no signed overflow."""
+    main = tmp_path / "main.cpp"
+    main.write_text(r"""
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+extern "C" {
+int probe_step(int, int, int, int, int, const int32_t *, const int32_t *, int *, int32_t *, int64_t *);
+int probe_prefill(int, int, int, int, int, int, int *, int64_t *);
+}
+int main() {
+    std::mt19937 rng(5);
+    auto upto = [&](int64_t n) { return (int32_t)(1 + rng() % n); };
+    int32_t ns[32];
+    int64_t work[2];
+    int ragged, out[4], done = 0;
+    const int32_t two[2] = {2097152, 1000000};
+    if (probe_step(2, 64, 8, 128, 524288, two, nullptr, &ragged, ns, work)) return 1;
+    for (int i = 0; i < 400; ++i) {
+        const int hkv = 1 << rng() % 4, g = 1 << rng() % 7, b = 1 + rng() % (i % 4 ? 8 : 32);
+        const int n = upto(1 << (1 + rng() % 23));
+        int32_t lens[32], nl[32];
+        for (int k = 0; k < b; ++k) lens[k] = upto(1 << (1 + rng() % 24)), nl[k] = upto(n);
+        done += !probe_step(b, g * hkv, hkv, 128, n, lens, i & 1 ? nl : nullptr, &ragged, ns, work);
+        done += !probe_prefill(b, g * hkv, hkv, 128, n, 1 + n / upto(64), out, work);
+    }
+    printf("done %d\n", done);
+    return done < 400;
+}
+""")
+    exe = tmp_path / "plans"
+    subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-fsanitize=undefined", "-fno-sanitize-recover=undefined",
+                    *plan_probe.SOURCES, str(main), "-o", str(exe)], check=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
