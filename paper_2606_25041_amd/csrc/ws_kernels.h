@@ -127,7 +127,7 @@ constexpr int LENS_IN_ARGS = 32;
 // class), and the launch runs KV head by KV head, class by class, so that the
 // contiguous range of items each XCD takes is a whole number of classes: an
 // even share of every stream.
-struct RaggedStream {
+struct alignas(16) RaggedStream {
     int32_t start;      // first item (INT32_MAX past the last stream)
     int32_t b;          // the stream
     int32_t ns;         // its splits
@@ -137,6 +137,7 @@ struct RaggedStream {
     FastDiv fd_ns;
     int32_t pad[2];     // (three 16-byte loads per lane)
 };
+static_assert(sizeof(RaggedStream) == 48 && alignof(RaggedStream) == 16, "read as three 16-byte vectors");
 struct RaggedPlan {
     int32_t n_items;    // items of one KV head
     int32_t deal, per_class;
