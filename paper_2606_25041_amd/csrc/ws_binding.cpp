@@ -77,13 +77,15 @@ struct Ints {
 };
 
 // a (host, device) pair of int32 arrays of the given shape (packed: any shape
-// of that many contiguous elements); None gives null pointers
+// of that many contiguous elements); None gives null pointers (so an empty
+// array, whose pointers are null too, is declined)
 bool int_pair(PyObject *o, std::initializer_list<int64_t> shape, bool packed, Ints &x) {
     if (o == Py_None) return true;
     if (!PyTuple_CheckExact(o) || PyTuple_GET_SIZE(o) != 2) return false;
     const at::Tensor *t[2] = {tensor(PyTuple_GET_ITEM(o, 0)), tensor(PyTuple_GET_ITEM(o, 1))};
     int64_t numel = 1;
     for (int64_t n : shape) numel *= n;
+    if (numel == 0) return false;
     for (const at::Tensor *p : t) {
         if (!p || p->scalar_type() != at::kInt) return false;
         if (packed ? (p->numel() != numel || !p->is_contiguous()) : !shaped(*p, shape)) return false;

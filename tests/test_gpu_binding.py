@@ -178,6 +178,16 @@ def test_prefill_and_gradient_forms(both, form):
         both(lambda: ws.block_causal_prefill_bwd(q, k, v, out, q, lse, offsets, workspace=small))
 
 
+def test_empty_arrays_are_not_taken_for_absent_ones(both):
+    """No block (or no stream) and an array of none of their starts (or
+    lengths): refused, as a NULL pointer, by the text and varlen entry points."""
+    q, k, v = _randn(B, 0, HQ, D), _randn(B, 0, HKV, D), _randn(B, 0, HKV, D)
+    off, none = _pair(np.zeros((B, 1))), _pair(np.zeros((B, 0)))
+    for got in (both(lambda: ws.block_causal_prefill(q, k, v, off, text_starts=none)),
+                both(lambda: ws.kv_append(_cache(B, 2, HKV, D), _pair([]), k[:0], v[:0], new_lens=_pair([])))):
+        assert isinstance(got, tuple) and got[0] is ws.WsError and "NULL" in got[1], got
+
+
 def test_calls_run_without_the_gil(tmp_path):
     """While a call is inside the library, other Python threads run (a launch
     may block on a full hardware queue).  The library's functions are replaced
