@@ -135,7 +135,7 @@ def _bind_native(lib):
             raise RuntimeError(f"{_build.BINDING} is not built; run `python -m paper_2606_25041_amd.build`")
         from . import _wsbinding
         _NATIVE = _wsbinding
-    _NATIVE.bind(*(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in (
+    _NATIVE.bind(PagedCache, *(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in (
         "ws_kv_append", "ws_kv_append_varlen", "ws_block_causal_attn_fwd", "ws_block_causal_attn_fwd_text",
         "ws_block_causal_attn_fwd_varlen", "ws_block_causal_attn_fwd_noalloc", "ws_block_causal_prefill",
         "ws_block_causal_prefill_text", "ws_block_causal_prefill_bwd", "ws_workspace_bytes",

@@ -39,16 +39,20 @@ struct Abi {
     decltype(&ws_step_workspace_bytes_varlen) workspace_bytes_varlen;
 } abi;
 
+PyObject *cache_class;   // PagedCache
+
 PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t n) {
-    if (n != (Py_ssize_t)(sizeof(Abi) / sizeof(void *))) {
-        PyErr_SetString(PyExc_TypeError, "one address per ABI function");
+    if (n != 1 + (Py_ssize_t)(sizeof(Abi) / sizeof(void *))) {
+        PyErr_SetString(PyExc_TypeError, "the cache class and one address per ABI function");
         return nullptr;
     }
-    for (Py_ssize_t i = 0; i < n; ++i) {
+    for (Py_ssize_t i = 1; i < n; ++i) {
         void *p = PyLong_AsVoidPtr(args[i]);
         if (PyErr_Occurred()) return nullptr;
-        ((void **)&abi)[i] = p;
+        ((void **)&abi)[i - 1] = p;
     }
+    Py_INCREF(args[0]);
+    Py_XSETREF(cache_class, args[0]);
     Py_RETURN_NONE;
 }
 
@@ -111,6 +115,8 @@ struct Paged : ws_paged_kv {
     at::Tensor hold[4];
 };
 bool paged(PyObject *cache, int64_t batch, Paged &d) {
+    // (another class may have a descriptor of its own: desc())
+    if ((PyObject *)Py_TYPE(cache) != cache_class) return false;
     PyObject *v[7] = {};
     bool ok = true;
     for (int i = 0; i < 7 && ok; ++i) ok = (v[i] = PyObject_GetAttr(cache, names[i])) != nullptr;
@@ -395,7 +401,7 @@ PyObject *prefill_bwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
 }
 
 PyMethodDef methods[] = {
-    {"bind", (PyCFunction)(void (*)())bind, METH_FASTCALL, "addresses of the C ABI's functions, in Abi's order"},
+    {"bind", (PyCFunction)(void (*)())bind, METH_FASTCALL, "the cache class, then the C ABI's addresses in Abi's order"},
     {"append", (PyCFunction)(void (*)())append, METH_FASTCALL, nullptr},
     {"step", (PyCFunction)(void (*)())step, METH_FASTCALL, nullptr},
     {"prefill", (PyCFunction)(void (*)())prefill, METH_FASTCALL, nullptr},

@@ -188,6 +188,22 @@ def test_empty_arrays_are_not_taken_for_absent_ones(both):
         assert isinstance(got, tuple) and got[0] is ws.WsError and "NULL" in got[1], got
 
 
+def test_a_cache_with_its_own_descriptor(both):
+    """A subclass that overrides desc() (here: keys and values read from other
+    pools than its attributes') is asked for it."""
+    class Other(ws.PagedCache):
+        def desc(self):
+            d = super().desc()
+            d.k_pool, d.v_pool = self.v_pool.data_ptr(), self.k_pool.data_ptr()
+            return d
+    q, k, v = _randn(B, L, HQ, D), _randn(B, L, HKV, D, seed=3), _randn(B, L, HKV, D, seed=4)
+    plain, lens = _cache(B, 2, HKV, D), _pair([70, 5])
+    other = Other(plain.k_pool, plain.v_pool, plain.page_table_host)
+    got = both(lambda: ws.block_causal_attn_fwd(q, k, v, other, lens))
+    swapped = ws.PagedCache(plain.v_pool, plain.k_pool, plain.page_table_host)
+    assert torch.equal(got, ws.block_causal_attn_fwd(q, k, v, swapped, lens))
+
+
 def test_calls_run_without_the_gil(tmp_path):
     """While a call is inside the library, other Python threads run (a launch
     may block on a full hardware queue).  The library's functions are replaced
@@ -219,7 +235,7 @@ def test_calls_run_without_the_gil(tmp_path):
     thread = threading.Thread(target=beside)
     thread.start()
     try:
-        native.bind(*[slow] * 9, size, size)
+        native.bind(ws.PagedCache, *[slow] * 9, size, size)
         for name, call in calls.items():
             before, start = turns[0], time.perf_counter()
             call()
