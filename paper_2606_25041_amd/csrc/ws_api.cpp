@@ -501,11 +501,12 @@ size_t bwd_part_bytes(int batch, int hkv) { return (size_t)batch * hkv * 2 * 128
 
 // The row data, then room for the parts that a sequence of short blocks
 // would be split into (the largest case is the plan's own choice: with longer
-// blocks it takes what fits).
+// blocks it takes what fits) on a whole chip.  Host arithmetic only: a program
+// may size its buffers before it has a device, or for another one; a partition
+// of fewer units splits less, or within the same room.
+constexpr int CHIP_CUS = 256;
 size_t bwd_workspace(int batch, int hq, int hkv, int seq) {
-    int cus = 0;
-    if (ws::current_device_cus(&cus)) cus = 0;   // no device: the row data only
-    const BwdPlan p = plan_bwd(cus, batch, hq, hkv, seq, nullptr, INT32_MAX);
+    const BwdPlan p = plan_bwd(CHIP_CUS, batch, hq, hkv, seq, nullptr, INT32_MAX);
     if (!p.split_tiles) return bwd_rows_bytes(batch, hq, seq);
     return bwd_part_offset(batch, hq, seq) + p.tile_start[p.split_tiles] * bwd_part_bytes(batch, hkv);
 }

@@ -5,6 +5,7 @@ import subprocess
 
 import pytest
 
+import paper_2606_25041_amd as ws
 from tests import plan_probe
 
 MAX_GRID = ((1 << 32) - 1) // 512   # work-groups of 512 threads in one launch
@@ -113,3 +114,13 @@ int main() {
                     *plan_probe.SOURCES, str(main), "-o", str(exe)], check=True)
     res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_gradient_workspace_is_host_arithmetic():
+    """The size query asks no device: the same bytes with none, on a partition
+    and on the whole chip, and room for the split sums of a short sequence."""
+    for batch, hq, hkv, seq in ((1, 32, 8, 2400), (1, 8, 1, 520), (2, 32, 8, 16384), (1, 6, 2, 100)):
+        got = {plan_probe.workspace_bytes(ws.WS_OP_PREFILL_BWD, batch, hq, hkv, seq, seq, cus) for cus in (0, 32, 256)}
+        assert len(got) == 1, (batch, hq, hkv, seq, got)
+        rows = -(-8 * batch * hq * seq // 256) * 256 + 4 * batch * seq
+        assert got.pop() > rows if seq in (2400, 520) else True
