@@ -203,6 +203,17 @@ StepPlan plan_step(int num_cus, int batch, int hq, int hkv, int lq, int64_t max_
     return p;
 }
 
+// A split step runs the instance without the code that writes final rows
+// (22 scalar spills against 24, f32 28, head dim 64 29): ~0.3 us less in front
+// of and behind the loop (GQA 32/8, 128 tokens over 8192: 27.9 -> 27.4 us).  Its
+// bf16 loop is 0.8 % slower per tile for no known reason (GQA 64/8, 300 tokens
+// over 60000, 314 tiles per split: 553 us against 558; equal at 59), so long
+// splits keep the common instance; its f32 loop is 1.5 % faster (same call, f32:
+// 565 -> 557 us).
+bool parts_only(const StepPlan &p, int64_t max_k, bool out_f32) {
+    return p.nsplit > 1 && (out_f32 || (max_k + 63) / 64 <= 48 * (int64_t)p.nsplit);
+}
+
 // Time, in tiles, of work-groups taken longest first by `cus` compute units:
 // groups of n equal items of `size` tiles, sizes not increasing.  Units with
 // the same load are kept together, so a round costs one entry.
@@ -902,7 +913,8 @@ int step_impl(ws_tensor4 q, ws_tensor4 k_new, ws_tensor4 v_new, const ws_paged_k
     int cus = 0;
     if (int e = ws::current_device_cus(&cus))
         return fail(WS_ERR_HIP, "cannot query the device's compute units (hip error %d)", e);
-    const StepPlan plan = plan_step(cus, batch, num_q_heads, kv->num_kv_heads, new_len, max_k, nl_host);
+    StepPlan plan = plan_step(cus, batch, num_q_heads, kv->num_kv_heads, new_len, max_k, nl_host);
+    plan.shape.parts_only = parts_only(plan, max_k, out.dtype == WS_DTYPE_F32);
     const size_t need_ws = step_workspace(plan, batch, num_q_heads, kv->num_kv_heads, new_len);
     if (noalloc) {
         // the library's per-device scratch array stands in for the workspace

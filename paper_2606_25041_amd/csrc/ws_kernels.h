@@ -206,6 +206,7 @@ struct TileShape {
     int nb;  // 32-query column blocks per wave
     int nw;  // waves per work-group
     int kg;  // key groups the waves are divided into (2: prefill only)
+    bool parts_only = false;   // step: the instance whose items all write partials
     int qtile() const { return nb * nw * 32 / kg; }
     // work-groups resident per CU (LDS and registers allow one)
     int groups_per_cu() const { return 1; }

@@ -80,8 +80,9 @@ __device__ __forceinline__ void append_share(const AttnArgs &a, int b, int kvh, 
 // call carries none of the others' scalars through its loop (the contiguous
 // prefill read its tile bases back from spilled registers) nor their code
 // through the instruction cache, where short launches spend their time.
-enum Kind { PREFILL_CONTIGUOUS, PREFILL_PAGED, STEP, STEP_RAGGED };
+enum Kind { PREFILL_CONTIGUOUS, PREFILL_PAGED, STEP, STEP_SPLIT, STEP_RAGGED };
 
+// STEP_SPLIT: every item writes partials, none rows of the output.
 // STEP_RAGGED: the streams have their own split counts (rp).
 struct NoPlan {};
 template <bool RAGGED>
@@ -95,7 +96,7 @@ using Plan = std::conditional_t<RAGGED, RaggedPlan, NoPlan>;
 // 256-row items leave compute units idle.
 template <int D, int NW, int NB, int KIND, bool F32, int KG>
 __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const Plan<KIND == STEP_RAGGED> rp) {
-    constexpr bool step = KIND == STEP || KIND == STEP_RAGGED;
+    constexpr bool step = KIND == STEP || KIND == STEP_SPLIT || KIND == STEP_RAGGED;
     constexpr bool RAGGED = KIND == STEP_RAGGED;
     constexpr int NT = NW * 64;
     constexpr int QT = NW * 32 * NB / KG;  // query rows per work-group
@@ -796,7 +797,8 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
     // time), and after the loop's last barrier nothing else touches it.
     // 3.3k tokens, GQA 40/8 x 128: 136 -> 131 us; GQA 64/8, 2 x 1.4k: 118 ->
     // 112 us; unchanged where an item runs many tiles.
-    if ((!step || nsplit == 1) && busy) {
+    const bool whole = KIND != STEP_SPLIT && (!step || nsplit == 1);   // this item's rows are final
+    if (whole && busy) {
         // (the lane is hidden from the optimiser, so that nothing derived from
         // it here is computed ahead of the loop and held in registers there)
         int ln = lane;
@@ -853,7 +855,7 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
         const int r = row[n];
         if (r >= (int)nrows) continue;
         const int t = tok[n], h = hqr[n];
-        if (!step || nsplit == 1) {
+        if (whole) {
             if (a.lse && hf == 0)
                 a.lse[((int64_t)b * a.Hq + h) * a.Lq + t] = (m[n] + __builtin_amdgcn_logf(lt)) * 0.69314718055994531f;
         } else if constexpr (!F32) {
@@ -1118,11 +1120,12 @@ int launch_prefill_t(const AttnArgs &a, int key_groups, hipStream_t st) {
 }
 
 template <int D>
-int launch_attn_d(const AttnArgs &a, const RaggedPlan *rag, int key_groups, hipStream_t st) {
+int launch_attn_d(const AttnArgs &a, const RaggedPlan *rag, TileShape shape, hipStream_t st) {
     return rag ? launch_attn_t<D, STEP_RAGGED, 1>(a, *rag, st)
-         : a.mode == MODE_STEP ? launch_attn_t<D, STEP, 1>(a, NoPlan{}, st)
-         : a.paged ? launch_prefill_t<D, PREFILL_PAGED>(a, key_groups, st)
-                   : launch_prefill_t<D, PREFILL_CONTIGUOUS>(a, key_groups, st);
+         : a.mode == MODE_STEP ? shape.parts_only ? launch_attn_t<D, STEP_SPLIT, 1>(a, NoPlan{}, st)
+                                                  : launch_attn_t<D, STEP, 1>(a, NoPlan{}, st)
+         : a.paged ? launch_prefill_t<D, PREFILL_PAGED>(a, shape.kg, st)
+                   : launch_prefill_t<D, PREFILL_CONTIGUOUS>(a, shape.kg, st);
 }
 
 template <int D, bool VL, bool RAGGED>
@@ -1164,8 +1167,8 @@ int launch_combine_d(const AttnArgs &a, const RaggedPlan *rag, hipStream_t st) {
 int launch_attention(const AttnArgs &a, const RaggedPlan *rag, int head_dim, TileShape shape, void *stream) {
     hipStream_t st = (hipStream_t)stream;
     if (shape.nw != 8 || shape.nb != 1) return (int)hipErrorInvalidValue;
-    if (head_dim == 128) return launch_attn_d<128>(a, rag, shape.kg, st);
-    if (head_dim == 64) return launch_attn_d<64>(a, rag, shape.kg, st);
+    if (head_dim == 128) return launch_attn_d<128>(a, rag, shape, st);
+    if (head_dim == 64) return launch_attn_d<64>(a, rag, shape, st);
     return (int)hipErrorInvalidValue;
 }
 
