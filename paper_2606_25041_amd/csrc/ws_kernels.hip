@@ -797,8 +797,13 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
     // time), and after the loop's last barrier nothing else touches it.
     // 3.3k tokens, GQA 40/8 x 128: 136 -> 131 us; GQA 64/8, 2 x 1.4k: 118 ->
     // 112 us; unchanged where an item runs many tiles.
+    // A step of at most 64 packed rows stores them from the registers instead:
+    // one or two waves hold them, and the exchange is latency at the end of the
+    // launch (32 streams of 24 rows over 1000 keys: 30.1 us through LDS, 29.3
+    // direct; f32 30.3 and 29.4; 64 rows 10.4 and 9.8, 128 rows 10.8 and 12.0).
     const bool whole = KIND != STEP_SPLIT && (!step || nsplit == 1);   // this item's rows are final
-    if (whole && busy) {
+    const bool direct = KIND == STEP && a.nrows <= 64;
+    if (whole && busy && !direct) {
         // (the lane is hidden from the optimiser, so that nothing derived from
         // it here is computed ahead of the loop and held in registers there)
         int ln = lane;
@@ -856,6 +861,26 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
         if (r >= (int)nrows) continue;
         const int t = tok[n], h = hqr[n];
         if (whole) {
+            if (direct) {
+                const float inv = lt > 0.f ? 1.f / lt : 0.f;
+                const int64_t ofs = b * a.o_sb + (int64_t)t * a.o_st + h * a.o_sh + 4 * hf;
+#pragma unroll
+                for (int md = 0; md < MD; ++md)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        if constexpr (F32) {
+                            f32x4 val;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) val[e] = o[n][md][4 * g + e] * inv;
+                            *(f32x4 *)((float *)a.out + ofs + 32 * md + 8 * g) = val;
+                        } else {
+                            u32x2 val;
+                            val[0] = pack_bf16x2(o[n][md][4 * g + 0] * inv, o[n][md][4 * g + 1] * inv);
+                            val[1] = pack_bf16x2(o[n][md][4 * g + 2] * inv, o[n][md][4 * g + 3] * inv);
+                            *(u32x2 *)((uint16_t *)a.out + ofs + 32 * md + 8 * g) = val;
+                        }
+                    }
+            }
             if (a.lse && hf == 0)
                 a.lse[((int64_t)b * a.Hq + h) * a.Lq + t] = (m[n] + __builtin_amdgcn_logf(lt)) * 0.69314718055994531f;
         } else if constexpr (!F32) {

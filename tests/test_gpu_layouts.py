@@ -77,3 +77,30 @@ def test_backward_fused_qkv_gradient_views():
     assert torch.equal(dqkv[:, :, :Hq], rq)
     assert torch.equal(dqkv[:, :, Hq:Hq + Hkv], rk)
     assert torch.equal(dqkv[:, :, Hq + Hkv:], rv)
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("G,Lq", [(1, 1), (3, 10), (3, 11), (1, 63), (1, 64), (1, 65), (8, 8), (8, 9)])
+def test_unsplit_step_rows(G, Lq, D, f32):
+    """Unsplit steps around 32 and 64 packed rows per KV head, where their
+    rows leave in another way: into a view with gaps between heads and tokens,
+    every output and lse against the oracle, the gaps untouched."""
+    B, Hkv, n = 2, 2, 20
+    wl = inputs.step_workload("rows", B, G * Hkv, Hkv, D, Lq, [n] * B, seed=300 + Lq + D)
+    assert ws.step_plan(B, G * Hkv, Hkv, Lq, wl.cache_lens)[0] == 1
+    cache = gs.device_cache(wl, wl.cache_lens)
+    dt = torch.float32 if f32 else torch.bfloat16
+    whole = torch.full((B, Lq + 1, G * Hkv + 2, D), 7.0, dtype=dt, device=gs.dev())
+    out = whole[:, :Lq, 1:G * Hkv + 1]
+    gs.say(f"[gpu] unsplit step of {G * Lq} rows, D={D}, f32={f32}")
+    _, lse = ws.block_causal_attn_fwd(*(gs.to_dev_bf16(t) for t in (wl.q, wl.k_new, wl.v_new)), cache, wl.cache_lens,
+                                      out=out, want_lse=True)
+    torch.cuda.synchronize()
+    ref, rl = oracle.step(*(inputs.bf16_bits(t) for t in (wl.q, wl.k[:, :n], wl.v[:, :n])), wl.cache_lens,
+                          inputs.bf16_bits(wl.k_new), inputs.bf16_bits(wl.v_new), wl.scale)
+    err = np.abs(out.double().cpu().numpy() - ref)
+    assert err.max() <= gs.MAX_ABS and err.mean() <= gs.MEAN_ABS, (err.max(), err.mean())
+    assert np.abs(lse.double().cpu().numpy() - rl).max() <= gs.LSE_ABS
+    out.fill_(7.0)
+    assert bool((whole == 7.0).all())
