@@ -25,11 +25,30 @@ class _Declines:
     append = step = prefill = prefill_bwd = _none
 
 
+class _Watched:
+    """The native marshalling, and whether it took the calls made through it."""
+
+    def __init__(self, native):
+        self.taken = []
+        for name in ("append", "step", "prefill", "prefill_bwd"):
+            setattr(self, name, self._watch(getattr(native, name)))
+
+    def _watch(self, f):
+        def call(*args):
+            got = f(*args)
+            self.taken.append(got is not None)
+            return got
+        return call
+
+
 @pytest.fixture
 def both(monkeypatch):
+    """Calls f through the native and through the Python marshalling, and
+    compares.  taken: whether the native one is to take the call (or decline it
+    before anything is enqueued); None: it is not asked."""
     ws.library()
 
-    def call(f):
+    def call(f, taken):
         def once():
             try:
                 r = f()
@@ -37,7 +56,10 @@ def both(monkeypatch):
                 return type(e), str(e)
             torch.cuda.synchronize()
             return r
+        watched = _Watched(ws._NATIVE)
+        monkeypatch.setattr(ws, "_NATIVE", watched)
         native = once()
+        assert watched.taken == ([] if taken is None else [taken]), (watched.taken, taken)
         monkeypatch.setattr(ws, "_NATIVE", _Declines())
         python = once()
         monkeypatch.undo()
@@ -80,6 +102,8 @@ STEP_FORMS = {
     "scale_zero": dict(scale=0.0), "text_range": dict(text_starts=[0, 21]), "workspace_small": dict(workspace="small"),
     "table_rows": dict(cache="one"), "out_shape": dict(out="short"), "q_cpu": dict(out="cpu"),
 }
+STEP_TAKEN = {"plain", "f32_lse", "scale", "fuse", "text", "new_lens", "new_lens_column", "out", "strided", "workspace",
+              "lse_given", "scale_zero", "workspace_small"}
 
 
 @pytest.mark.parametrize("form", sorted(STEP_FORMS))
@@ -123,7 +147,7 @@ def test_step_forms(both, form):
         rows = r if isinstance(r, tuple) else (r,)
         return [rows[0][b, :real[b]].clone() for b in range(B)] + [x.clone() for x in rows[1:]] + \
             [cache.k_pool.clone(), cache.v_pool.clone()]
-    both(f)
+    both(f, form in STEP_TAKEN)
 
 
 @pytest.mark.parametrize("form", ["plain", "lse", "lens_list", "out_none", "out_shape"])
@@ -136,7 +160,7 @@ def test_noalloc_forms(both, form):
     def f():
         r = ws.block_causal_attn_fwd_noalloc(q, k, v, cache, [70, 5] if form == "lens_list" else lens, out, lse=lse)
         return [r.clone()] + ([lse.clone()] if lse is not None else [])
-    both(f)
+    both(f, None if form == "out_none" else form in ("plain", "lse"))
 
 
 @pytest.mark.parametrize("form", ["plain", "list", "new_lens", "new_lens_list", "strided", "shape", "capacity", "table"])
@@ -153,7 +177,7 @@ def test_append_forms(both, form):
             cache.page_table_host = cache.page_table_host[:1]
         ws.kv_append(cache, lens, k[:, :, :1] if form == "shape" else k, v, new_lens=nl)
         return [cache.k_pool, cache.v_pool]
-    both(f)
+    both(f, form in ("plain", "new_lens", "strided", "capacity"))
 
 
 @pytest.mark.parametrize("form", ["plain", "list", "paged", "paged_heads", "text", "f32_lse", "cache_too", "empty",
@@ -169,13 +193,14 @@ def test_prefill_and_gradient_forms(both, form):
     heads = {"paged_heads": HKV, "heads_wrong": 1}.get(form)
     kw = dict(cache=cache, num_kv_heads=heads, text_starts=text,
               out_dtype=torch.float32 if form == "f32_lse" else torch.bfloat16)
-    both(lambda: ws.block_causal_prefill(q, kk, vv, offsets, want_lse=form == "f32_lse", **kw))
+    both(lambda: ws.block_causal_prefill(q, kk, vv, offsets, want_lse=form == "f32_lse", **kw), form not in ("list", "v_none"))
     if form in ("plain", "list", "text", "offsets", "empty"):
         out, lse = ws.block_causal_prefill(q, k, v, _pair(off), want_lse=True, text_starts=text)
-        both(lambda: ws.block_causal_prefill_bwd(q, k, v, out, q, lse, offsets, text_starts=text))
-        both(lambda: ws.block_causal_prefill_bwd(q, k, v[:, :, :1], out, q, lse, offsets))
+        taken = form not in ("list", "empty")
+        both(lambda: ws.block_causal_prefill_bwd(q, k, v, out, q, lse, offsets, text_starts=text), taken)
+        both(lambda: ws.block_causal_prefill_bwd(q, k, v[:, :, :1], out, q, lse, offsets), False)
         small = torch.empty(16, dtype=torch.uint8, device="cuda")
-        both(lambda: ws.block_causal_prefill_bwd(q, k, v, out, q, lse, offsets, workspace=small))
+        both(lambda: ws.block_causal_prefill_bwd(q, k, v, out, q, lse, offsets, workspace=small), taken)
 
 
 def test_empty_arrays_are_not_taken_for_absent_ones(both):
@@ -183,8 +208,8 @@ def test_empty_arrays_are_not_taken_for_absent_ones(both):
     lengths): refused, as a NULL pointer, by the text and varlen entry points."""
     q, k, v = _randn(B, 0, HQ, D), _randn(B, 0, HKV, D), _randn(B, 0, HKV, D)
     off, none = _pair(np.zeros((B, 1))), _pair(np.zeros((B, 0)))
-    for got in (both(lambda: ws.block_causal_prefill(q, k, v, off, text_starts=none)),
-                both(lambda: ws.kv_append(_cache(B, 2, HKV, D), _pair([]), k[:0], v[:0], new_lens=_pair([])))):
+    for got in (both(lambda: ws.block_causal_prefill(q, k, v, off, text_starts=none), False),
+                both(lambda: ws.kv_append(_cache(B, 2, HKV, D), _pair([]), k[:0], v[:0], new_lens=_pair([])), False)):
         assert isinstance(got, tuple) and got[0] is ws.WsError and "NULL" in got[1], got
 
 
@@ -199,7 +224,7 @@ def test_a_cache_with_its_own_descriptor(both):
     q, k, v = _randn(B, L, HQ, D), _randn(B, L, HKV, D, seed=3), _randn(B, L, HKV, D, seed=4)
     plain, lens = _cache(B, 2, HKV, D), _pair([70, 5])
     other = Other(plain.k_pool, plain.v_pool, plain.page_table_host)
-    got = both(lambda: ws.block_causal_attn_fwd(q, k, v, other, lens))
+    got = both(lambda: ws.block_causal_attn_fwd(q, k, v, other, lens), False)
     swapped = ws.PagedCache(plain.v_pool, plain.k_pool, plain.page_table_host)
     assert torch.equal(got, ws.block_causal_attn_fwd(q, k, v, swapped, lens))
 
