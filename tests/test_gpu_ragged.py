@@ -1,8 +1,9 @@
 """Steps over streams of very different lengths, whose plan gives every stream
-its own KV split count: every output against the oracle, at the edges of the
-plan (one stream far longer than the rest, streams with one split beside
-streams with many, empty caches, several query tiles, KV head counts that do
-and do not divide the 8 XCDs, 2 and 32 streams), with segments, padded blocks,
+its own KV split count (checked of every case): every output against the
+oracle, at the edges of the plan (one stream far longer than the rest, streams
+with one split beside streams with many, no splits at all in more than one
+round of items, empty caches, several query tiles, KV head counts that do and
+do not divide the 8 XCDs, 2 and 32 streams), with segments, padded blocks,
 both output types, lse and the fused append (pool bit for bit)."""
 import numpy as np
 import pytest
@@ -12,19 +13,21 @@ import oracle
 import paper_2606_25041_amd as ws
 from paper_2606_25041_amd import inputs
 from tests import gpu_support as gs
+from tests import plan_probe
 
 pytestmark = pytest.mark.gpu
 
 CASES = [
     # Hq, Hkv, D, Lq, caches, new_lens, starts, f32
     (8, 8, 128, 3, [9000, 0, 70, 1], None, [0, 0, 0, 0], False),
-    (16, 2, 128, 40, [5000, 17], None, None, False),
-    (6, 3, 64, 20, [12000, 64, 1000], [20, 1, 7], None, True),
+    (16, 2, 128, 40, [9000, 17, 40, 0, 5], None, None, False),
+    (6, 3, 64, 20, [12000, 64, 1000, 40, 200], [20, 1, 7, 20, 2], None, True),
     (12, 4, 128, 90, [4000, 300, 300, 8], [90, 33, 64, 1], [80, 33, 0, 0], False),
     (24, 24, 128, 30, [2500, 3], None, None, True),
     (4, 1, 64, 300, [7000, 129, 0], None, [290, 300, 0], False),
     (2, 2, 64, 1, [6000] + [5] * 31, None, None, False),
-    (2, 1, 128, 2, [40000, 1], None, [0, 1], True),
+    (16, 8, 128, 2, [40000, 1], None, [0, 1], True),
+    (24, 24, 64, 3, [900, 3, 500] + [40] * 13, None, None, False),   # unsplit
 ]
 
 
@@ -34,6 +37,9 @@ def test_ragged_step(case):
     B = len(caches)
     wl = inputs.step_workload(f"ragged_{case}", B, Hq, Hkv, D, Lq, caches, seed=4000 + case, fuse_append=True)
     gs.say(f"[gpu] ragged step {case}: {Hq}/{Hkv}x{D} Lq={Lq} caches={caches}")
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    plan = plan_probe.step(B, Hq, Hkv, D, Lq, caches, nls, cus=cus)
+    assert plan.ragged and (max(plan.splits) > 1 or plan.items > cus), plan
     cache = ws.PagedCache.allocate(wl.num_pages, Hkv, D, torch.from_numpy(wl.page_table), fill_bits=0x7FC1)
     for b in range(B):
         n = int(wl.cache_lens[b])
