@@ -371,7 +371,12 @@ bool plan_ragged(ws::RaggedPlan &r, int num_cus, const StepPlan &uni, int batch,
         return items <= cap;
     };
     // Lengths that hardly differ keep the common count, whose launch reads
-    // less: a 10 % gain is asked for, without splits a ratio of 5 / 4.
+    // less: a gain of 10 % and of two tiles is asked for, without splits a ratio
+    // of 5 / 4.  (The per-stream kernel itself costs about a tile: of 79 drawn
+    // steps, 37 of a modelled gain of one tile ran at 0.87x to 1.16x of the
+    // common plan's speed, 28 of them below 1 (GQA 16/4 x 64, 174 tokens over 916
+    // and 226: 14.4 us against 13.1); from two tiles on 42 at 0.93x to 2.6x, 2
+    // below 1.)
     // Where every item has a compute unit of its own, no order of them helps
     // (24 or 32 streams of 8 KV heads, 3 new tokens: 37.2 and 39.1 us, through
     // this plan 37.7 and 40.3).
@@ -384,7 +389,7 @@ bool plan_ragged(ws::RaggedPlan &r, int num_cus, const StepPlan &uni, int batch,
         const int uniform = best;
         bool more = attempt(1);
         for (int s = 2; more && s <= WS_MAX_SPLITS; ++s) more = attempt(s);
-        if (10 * (int64_t)best > 9 * (int64_t)uniform) return false;
+        if (10 * (int64_t)best > 9 * (int64_t)uniform || uniform - best < 2) return false;
     }
     int64_t at = 0, slot = 0;
     r.max_nsplit = 1;

@@ -124,3 +124,18 @@ def test_gradient_workspace_is_host_arithmetic():
         assert len(got) == 1, (batch, hq, hkv, seq, got)
         rows = -(-8 * batch * hq * seq // 256) * 256 + 4 * batch * seq
         assert got.pop() > rows if seq in (2400, 520) else True
+
+
+@pytest.mark.parametrize("hq,hkv,d,new,lens,ragged", [
+    (16, 4, 64, 174, [916, 226], False),
+    (32, 8, 128, 246, [2, 394], False),
+    (12, 4, 128, 100, [50, 900], False),
+    (12, 4, 128, 3, [1567, 2299, 1953, 2354], False),
+    (64, 8, 128, 3, [32768, 9001, 2750, 517], True),
+    (16, 4, 64, 37, [5003, 1200, 64, 2777, 333, 0], True),
+    (24, 24, 128, 256, [63, 1332, 2019], True),
+])
+def test_per_stream_splits_have_to_win_two_tiles(hq, hkv, d, new, lens, ragged):
+    """The per-stream kernel costs about a key tile more than the common one,
+    which a modelled gain of one tile does not pay for."""
+    assert plan_probe.step(len(lens), hq, hkv, d, new, lens).ragged == ragged
