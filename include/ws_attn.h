@@ -195,9 +195,11 @@ int ws_kv_append(const ws_paged_kv *kv, int32_t batch,
  * The library splits long caches into KV partitions merged by a second
  * launch.  The partition count is planned for the compute units of the
  * current device (queried once per device; ws_step_plan shows the plan for
- * any count).  The environment variable WS_SPLITS (1..32) overrides it for
- * tuning; it is read once per process, at the first call that plans a
- * step, so workspace queries and calls always agree.
+ * any count).  Up to 32 streams of different lengths may each get a count of
+ * their own, within the workspace of the common one.  The environment
+ * variable WS_SPLITS (1..32) overrides the count for tuning; it is read once
+ * per process, at the first call that plans a step, so workspace queries and
+ * calls always agree.
  * Errors: WS_ERR_NULL, WS_ERR_SHAPE, WS_ERR_UNSUPPORTED, WS_ERR_ALIGN,
  * WS_ERR_HEADS, WS_ERR_CAPACITY, WS_ERR_PAGE, WS_ERR_WORKSPACE, WS_ERR_HIP.
  */
@@ -403,8 +405,9 @@ int ws_block_causal_prefill_bwd(ws_tensor4 q, ws_tensor4 k, ws_tensor4 v, ws_ten
  * WS_OP_STEP; num_kv_heads = the cache's; max_k = largest cache_lens[b] +
  * new_len), planned for the current device's compute units (0 when no
  * device is available).  WS_OP_PREFILL returns 0.  WS_OP_PREFILL_BWD
- * (max_q = max_k = seq_len): the bytes ws_block_causal_prefill_bwd needs
- * (pure host arithmetic).  Returns 0 for invalid arguments.
+ * (max_q = max_k = seq_len): the bytes ws_block_causal_prefill_bwd needs,
+ * with room for the sums it would split on a whole chip (pure host
+ * arithmetic: no device is asked).  Returns 0 for invalid arguments.
  */
 size_t ws_workspace_bytes(int32_t op, int32_t batch, int32_t num_q_heads, int32_t num_kv_heads,
                           int32_t max_q, int32_t max_k);
@@ -413,7 +416,9 @@ size_t ws_workspace_bytes(int32_t op, int32_t batch, int32_t num_q_heads, int32_
  * ws_step_plan -- the launch plan of a streaming step (host only; nothing
  * is enqueued).  Work items are (stream, KV head, 256-row query tile, KV
  * split); the plan picks the KV split count for num_cus compute units
- * (0: the current device's) and reports the workspace the step needs:
+ * (0: the current device's), common to all streams, and reports the workspace
+ * the step needs (over streams of different lengths the launch may use other
+ * counts per stream, in the same workspace):
  * the value ws_block_causal_attn_fwd(_text) (new_lens_host NULL) or
  * ws_block_causal_attn_fwd_varlen (new_lens_host: int32 [batch]) checks
  * on a device with that many compute units.
