@@ -314,8 +314,9 @@ bool deal_pays(int cus, const ws::AttnArgs &a, int64_t groups, int deal, ws::Til
 // times within 2 % the fewest splits.  The streams' splits share the partial
 // slots of plan_step's plan (its split count x batch), so the workspace is
 // the same; a stream with one split writes its output itself and needs none.
+// slot_bytes: output values of one partial slot.
 bool plan_ragged(ws::RaggedPlan &r, int num_cus, const StepPlan &uni, int batch, int hq, int hkv, int lq,
-                 const int32_t *cache_lens, const int32_t *nl, const int32_t *text) {
+                 const int32_t *cache_lens, const int32_t *nl, const int32_t *text, int64_t slot_bytes) {
     if (batch < 2 || batch > ws::LENS_IN_ARGS || split_override()) return false;
     const int64_t qt = uni.shape.qtile(), G = hq / hkv;
     struct Stream { int tiles, q, b; } st[ws::LENS_IN_ARGS];
@@ -371,12 +372,15 @@ bool plan_ragged(ws::RaggedPlan &r, int num_cus, const StepPlan &uni, int batch,
         return items <= cap;
     };
     // Lengths that hardly differ keep the common count, whose launch reads
-    // less: a gain of 10 % and of two tiles is asked for, without splits a ratio
-    // of 5 / 4.  (The per-stream kernel itself costs about a tile: of 79 drawn
-    // steps, 37 of a modelled gain of one tile ran at 0.87x to 1.16x of the
-    // common plan's speed, 28 of them below 1 (GQA 16/4 x 64, 174 tokens over 916
-    // and 226: 14.4 us against 13.1); from two tiles on 42 at 0.93x to 2.6x, 2
-    // below 1.)
+    // less: a gain of 10 % and of 1.75 tiles is asked for, without splits a ratio
+    // of 5 / 4.  The per-stream kernel itself costs about a tile (GQA 16/4 x 64,
+    // 174 tokens over 916 and 226, a modelled gain of one: 14.4 us against 13.1);
+    // fewer partials count as gained, a tile for every 8.2 MB not written and
+    // read back (f32, GQA 64/8, 40 tokens over 134, 76, 560 and 22: 16.9 us
+    // against 19.6).  Of 260 drawn steps that win 10 % by the model, all taken
+    // ran at 0.83x to 2.5x of the common plan's speed, 63 of them below 0.97; the
+    // rule takes 131, 5 of them below 0.97 (least 0.92), and leaves none out
+    // that won more than 12 %.
     // Where every item has a compute unit of its own, no order of them helps
     // (24 or 32 streams of 8 KV heads, 3 new tokens: 37.2 and 39.1 us, through
     // this plan 37.7 and 40.3).
@@ -389,7 +393,10 @@ bool plan_ragged(ws::RaggedPlan &r, int num_cus, const StepPlan &uni, int batch,
         const int uniform = best;
         bool more = attempt(1);
         for (int s = 2; more && s <= WS_MAX_SPLITS; ++s) more = attempt(s);
-        if (10 * (int64_t)best > 9 * (int64_t)uniform || uniform - best < 2) return false;
+        int64_t used = 0;
+        for (int p = 0; p < batch; ++p) used += best_ns[p] > 1 ? best_ns[p] : 0;
+        const double gain = uniform - best + (double)((room - used) * slot_bytes) / 8.2e6;
+        if (10 * (int64_t)best > 9 * (int64_t)uniform || gain < 1.75) return false;
     }
     int64_t at = 0, slot = 0;
     r.max_nsplit = 1;
@@ -983,8 +990,9 @@ int step_impl(ws_tensor4 q, ws_tensor4 k_new, ws_tensor4 v_new, const ws_paged_k
     if (!finish_work(a)) return fail(WS_ERR_SHAPE, "too many work items");
     // streams of different lengths: per-stream splits
     ws::RaggedPlan rag;
+    const int64_t slot_bytes = (int64_t)a.Hkv * a.nrb * 32 * kv->head_dim * (a.out_f32 ? 4 : 2);
     const bool ragged = plan_ragged(rag, cus, plan, batch, num_q_heads, kv->num_kv_heads, new_len, cache_lens_host,
-                                    nl_host, text_host);
+                                    nl_host, text_host, slot_bytes);
     if (ragged) {
         a.per_group = rag.deal * rag.per_class;
         a.fd_group = ws::fastdiv_make((uint32_t)a.per_group);

@@ -48,18 +48,19 @@ void probe_cus(int cus) { g_cus = cus; }
 // Plans a step; lens, nl (nullable) and ns are [batch].  Returns the status;
 // *ragged: every stream has its own split count; ns: those counts; work: work
 // items, grid work-groups.
-int probe_step(int batch, int hq, int hkv, int d, int new_len, const int32_t *lens, const int32_t *nl, int *ragged,
+int probe_step(int batch, int hq, int hkv, int d, int new_len, const int32_t *lens, const int32_t *nl, int f32, int *ragged,
                int32_t *ns, int64_t *work) {
     int64_t pages = 1;
     for (int b = 0; b < batch; ++b) pages = std::max<int64_t>(pages, lens[b] / 64 + 1);
     const std::vector<int32_t> table((size_t)(batch * pages), 0);
     const ws_paged_kv kv{g_mem, g_mem, (int32_t *)g_mem, table.data(), 1, WS_PAGE_SIZE, (int32_t)pages, hkv, d};
-    const ws_tensor4 q = tensor(WS_DTYPE_BF16, new_len, hq, d), k = tensor(WS_DTYPE_BF16, new_len, hkv, d);
+    const ws_tensor4 q = tensor(WS_DTYPE_BF16, new_len, hq, d), k = tensor(WS_DTYPE_BF16, new_len, hkv, d),
+                     out = tensor(f32 ? WS_DTYPE_F32 : WS_DTYPE_BF16, new_len, hq, d);
     memset(&g_seen, 0, sizeof g_seen);
     const int32_t *dev = (const int32_t *)g_mem;
     const int rc = nl ? ws_block_causal_attn_fwd_varlen(q, k, k, &kv, lens, dev, nl, dev, nullptr, nullptr, batch, new_len,
-                                                        hq, 0.1f, 0, q, nullptr, g_mem, (size_t)1 << 60, nullptr)
-                      : ws_block_causal_attn_fwd(q, k, k, &kv, lens, dev, batch, new_len, hq, 0.1f, 0, q, nullptr, g_mem,
+                                                        hq, 0.1f, 0, out, nullptr, g_mem, (size_t)1 << 60, nullptr)
+                      : ws_block_causal_attn_fwd(q, k, k, &kv, lens, dev, batch, new_len, hq, 0.1f, 0, out, nullptr, g_mem,
                                                  (size_t)1 << 60, nullptr);
     *ragged = g_seen.ragged;
     for (int b = 0; b < batch; ++b) ns[b] = g_seen.ragged ? g_seen.rag.ns[b] : g_seen.attn.nsplit;

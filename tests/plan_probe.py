@@ -28,7 +28,7 @@ def _ints(x):
     return np.ascontiguousarray(x, np.int32)
 
 
-def step(batch, hq, hkv, d, new_len, lens, new_lens=None, cus=256):
+def step(batch, hq, hkv, d, new_len, lens, new_lens=None, f32=False, cus=256):
     """Status of a step and its plan: ragged (every stream has its own split
     count), splits per stream, work items and work-groups launched."""
     lib = _lib()
@@ -36,7 +36,7 @@ def step(batch, hq, hkv, d, new_len, lens, new_lens=None, cus=256):
     lens, ns, work, ragged = _ints(lens), np.zeros(batch, np.int32), (ctypes.c_int64 * 2)(), ctypes.c_int(0)
     nl = None if new_lens is None else _ints(new_lens)
     rc = lib.probe_step(batch, hq, hkv, d, new_len, ctypes.c_void_p(lens.ctypes.data),
-                        None if nl is None else ctypes.c_void_p(nl.ctypes.data), ctypes.byref(ragged),
+                        None if nl is None else ctypes.c_void_p(nl.ctypes.data), int(f32), ctypes.byref(ragged),
                         ctypes.c_void_p(ns.ctypes.data), work)
     return SimpleNamespace(status=rc, ragged=bool(ragged.value), splits=ns.tolist(), items=work[0], launched=work[1])
 

@@ -38,7 +38,7 @@ def test_ragged_step(case):
     wl = inputs.step_workload(f"ragged_{case}", B, Hq, Hkv, D, Lq, caches, seed=4000 + case, fuse_append=True)
     gs.say(f"[gpu] ragged step {case}: {Hq}/{Hkv}x{D} Lq={Lq} caches={caches}")
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    plan = plan_probe.step(B, Hq, Hkv, D, Lq, caches, nls, cus=cus)
+    plan = plan_probe.step(B, Hq, Hkv, D, Lq, caches, nls, f32, cus=cus)
     assert plan.ragged and (max(plan.splits) > 1 or plan.items > cus), plan
     cache = ws.PagedCache.allocate(wl.num_pages, Hkv, D, torch.from_numpy(wl.page_table), fill_bits=0x7FC1)
     for b in range(B):

@@ -86,7 +86,7 @@ def test_plans_of_extreme_sizes_stay_in_range(tmp_path):
 #include <cstdlib>
 #include <random>
 extern "C" {
-int probe_step(int, int, int, int, int, const int32_t *, const int32_t *, int *, int32_t *, int64_t *);
+int probe_step(int, int, int, int, int, const int32_t *, const int32_t *, int, int *, int32_t *, int64_t *);
 int probe_prefill(int, int, int, int, int, int, int *, int64_t *);
 }
 int main() {
@@ -96,13 +96,13 @@ int main() {
     int64_t work[2];
     int ragged, out[4], done = 0;
     const int32_t two[2] = {2097152, 1000000};
-    if (probe_step(2, 64, 8, 128, 524288, two, nullptr, &ragged, ns, work)) return 1;
+    if (probe_step(2, 64, 8, 128, 524288, two, nullptr, 0, &ragged, ns, work)) return 1;
     for (int i = 0; i < 400; ++i) {
         const int hkv = 1 << rng() % 4, g = 1 << rng() % 7, b = 1 + rng() % (i % 4 ? 8 : 32);
         const int n = upto(1 << (1 + rng() % 23));
         int32_t lens[32], nl[32];
         for (int k = 0; k < b; ++k) lens[k] = upto(1 << (1 + rng() % 24)), nl[k] = upto(n);
-        done += !probe_step(b, g * hkv, hkv, 128, n, lens, i & 1 ? nl : nullptr, &ragged, ns, work);
+        done += !probe_step(b, g * hkv, hkv, 128, n, lens, i & 1 ? nl : nullptr, i & 2, &ragged, ns, work);
         done += !probe_prefill(b, g * hkv, hkv, 128, n, 1 + n / upto(64), out, work);
     }
     printf("done %d\n", done);
@@ -126,16 +126,18 @@ def test_gradient_workspace_is_host_arithmetic():
         assert got.pop() > rows if seq in (2400, 520) else True
 
 
-@pytest.mark.parametrize("hq,hkv,d,new,lens,ragged", [
-    (16, 4, 64, 174, [916, 226], False),
-    (32, 8, 128, 246, [2, 394], False),
-    (12, 4, 128, 100, [50, 900], False),
-    (12, 4, 128, 3, [1567, 2299, 1953, 2354], False),
-    (64, 8, 128, 3, [32768, 9001, 2750, 517], True),
-    (16, 4, 64, 37, [5003, 1200, 64, 2777, 333, 0], True),
-    (24, 24, 128, 256, [63, 1332, 2019], True),
+@pytest.mark.parametrize("hq,hkv,d,new,lens,f32,ragged", [
+    (16, 4, 64, 174, [916, 226], False, False),
+    (32, 8, 128, 246, [2, 394], False, False),
+    (12, 4, 128, 100, [50, 900], False, False),
+    (12, 4, 128, 3, [1567, 2299, 1953, 2354], False, False),
+    (8, 8, 64, 40, [139, 144, 4, 33, 10, 103, 69, 199], True, False),
+    (64, 8, 128, 40, [134, 76, 560, 22], True, True),    # one tile, and 12 MB less of partials
+    (64, 8, 128, 3, [32768, 9001, 2750, 517], False, True),
+    (16, 4, 64, 37, [5003, 1200, 64, 2777, 333, 0], True, True),
+    (24, 24, 128, 256, [63, 1332, 2019], False, True),
 ])
-def test_per_stream_splits_have_to_win_two_tiles(hq, hkv, d, new, lens, ragged):
+def test_per_stream_splits_have_to_win_their_cost(hq, hkv, d, new, lens, f32, ragged):
     """The per-stream kernel costs about a key tile more than the common one,
-    which a modelled gain of one tile does not pay for."""
-    assert plan_probe.step(len(lens), hq, hkv, d, new, lens).ragged == ragged
+    which a modelled gain of one tile alone does not pay for."""
+    assert plan_probe.step(len(lens), hq, hkv, d, new, lens, f32=f32).ragged == ragged
