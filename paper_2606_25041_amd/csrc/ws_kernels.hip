@@ -44,6 +44,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "ws_kernels.h"
@@ -949,9 +950,10 @@ __global__ __launch_bounds__(NW * 64) void attn_kernel(const AttnArgs a, const P
 // blocks, head dim 128: 5.0 us against 5.4; 32 of 128, head dim 64: 5.7 against
 // 6.4); past that a unit's second work-group runs after its first, and 256 are
 // faster (21 splits of 76 blocks, head dim 128: 7.1 against 5.6 us, 16 of 128:
-// 6.0 against 5.3; 18 of 160, head dim 64: 6.8 against 5.7).  f32: 256 (128
-// measured 5 to 20 % slower from 76 blocks on, a few tenths of a us faster
-// below).
+// 6.0 against 5.3; 18 of 160, head dim 64: 6.8 against 5.7).  Blocks of streams
+// with one split do not count (24 of 72 merged, up to 29 splits: 5.4 against
+// 6.1).  f32: 256 (128 measured 5 to 20 % slower from 76 blocks on, a few tenths
+// of a us faster below).
 
 // bf16 output: split s holds o_s / l_s (bf16) and lse_s = m_s + log2(l_s);
 //   M = max_s lse_s,  L = sum_s 2^(lse_s - M),  o = sum_s 2^(lse_s - M) o_s / L.
@@ -1161,7 +1163,9 @@ int launch_combine_t(const AttnArgs &a, const Plan<RAGGED> &rp, int nsplit, hipS
     const int64_t blocks = (int64_t)a.B * a.Hkv * a.nrb;
     int cus = 0;
     if (int e = current_device_cus(&cus)) return e;
-    const int nt = !a.out_f32 && blocks * (per_blk / 128) <= cus ? 128 : 256;
+    int64_t merged = blocks;   // those that are not of a stream with one split
+    if constexpr (RAGGED) merged = std::count_if(rp.ns, rp.ns + a.B, [](int32_t n) { return n > 1; }) * (int64_t)a.Hkv * a.nrb;
+    const int nt = !a.out_f32 && merged * (per_blk / 128) <= cus ? 128 : 256;
     const dim3 grid((unsigned)(blocks * (per_blk / nt)));
     auto launch = [&](auto smax) {
         constexpr int SMAX = decltype(smax)::value;
