@@ -255,14 +255,18 @@ constexpr int64_t FEW_ROUNDS = 6;
 // two halves share (items half as long, twice as many), where few items leave
 // compute units idle or the longest sets the time.  Modelled as a longest-first
 // dispatch of the items on one XCD's compute units, in 64-key tiles (~1.75
-// us): a 256-row item takes the tiles its last row sees (mean of the streams)
-// and a fixed 2.5, a 128-row item half of its tiles at 1.12 (each step loads
-// two) and a fixed 3.5 (the halves are merged); it has to win 7 % (GQA 32/8,
-// 1.1k tokens 40.4 -> 31.8 us; 8 heads of 64, 1.8k tokens 35.8 -> 21.1; at 3.3k
-// tokens GQA 40/8 the two are equal and the 256-row tile stays).  The key ends
-// are the blocks': in one block of 1000 tokens every row sees them all, and 36
-// heads of it fill a round with 256-row items (36 us against 40 in two rounds
-// of 128-row items, which items taken as causal had promised to be shorter).
+// us).  With causal items a 256-row item i takes 4 (i + 1) and a fixed 2.5, a
+// 128-row item half its 2 (i + 1) tiles at 1.12 (each step loads two) and a
+// fixed 3.5 (the halves are merged); it has to win 7 % (GQA 32/8, 1.1k tokens
+// 40.4 -> 31.8 us; 8 heads of 64, 1.8k tokens 35.8 -> 21.1; at 3.3k tokens GQA
+// 40/8 the two are equal and the 256-row tile stays).  Long blocks are not
+// causal: in one block of 1000 tokens every row sees them all, and 36 heads of
+// it fill a round with 256-row items (36 us against 40 in two rounds of 128-row
+// ones).  So with the key ends of the blocks (mean of the streams; 1.06 a tile
+// and a fixed 3) it must not be slower by 2 % either: of 420 drawn prefills of
+// a round or more, both tiles timed, the causal model alone takes 82, 25 of them
+// slower by 3 % or more (up to 39 %), this 59, 8 of them (up to 16 %); what it
+// leaves out would have won 10 % at most.
 ws::TileShape plan_prefill(int num_cus, int batch, int hq, int seq, const int32_t *offsets, const int32_t *text,
                            int num_blocks) {
     constexpr int MAX = 64, ONE = 100;   // sizes in hundredths
@@ -272,6 +276,10 @@ ws::TileShape plan_prefill(int num_cus, int batch, int hq, int seq, const int32_
     const int64_t per = ((int64_t)batch * hq + ws::NUM_XCD - 1) / ws::NUM_XCD;   // items of a tile level per XCD
     if (cus < 1 || n2 > MAX || per * n1 > FEW_ROUNDS * (int64_t)cus) return s;
     ItemGroup g1[MAX], g2[MAX];
+    for (int i = 0; i < n1; ++i) g1[i] = {4 * (n1 - i) * ONE + 250, (int)per};
+    for (int i = 0; i < n2; ++i) g2[i] = {(n2 - i) * 112 + 350, (int)per};
+    g1[0].size = (seq + 63) / 64 * ONE + 250;   // the last tile may be short
+    if (100 * (int64_t)dispatch_time(cus, g2, n2) >= 93 * (int64_t)dispatch_time(cus, g1, n1)) return s;
     int64_t keys[MAX] = {};   // per 128-row tile: 64-key tiles its last row sees, over the streams
     for (int b = 0; b < batch; ++b) {
         const int32_t *off = offsets + (int64_t)b * (num_blocks + 1);
@@ -284,8 +292,8 @@ ws::TileShape plan_prefill(int num_cus, int batch, int hq, int seq, const int32_
     }
     auto tiles = [&](int i) -> int { return (int)(keys[i] * ONE / batch); };
     for (int i = 0; i < n1; ++i) g1[i] = {tiles(std::min(2 * (n1 - i) - 1, n2 - 1)) + 250, (int)per};
-    for (int i = 0; i < n2; ++i) g2[i] = {tiles(n2 - 1 - i) * 56 / 100 + 350, (int)per};
-    if (100 * (int64_t)dispatch_time(cus, g2, n2) < 93 * (int64_t)dispatch_time(cus, g1, n1)) s.kg = 2;
+    for (int i = 0; i < n2; ++i) g2[i] = {tiles(n2 - 1 - i) * 53 / 100 + 300, (int)per};
+    if (100 * (int64_t)dispatch_time(cus, g2, n2) < 102 * (int64_t)dispatch_time(cus, g1, n1)) s.kg = 2;
     return s;
 }
 
@@ -300,7 +308,7 @@ bool deal_pays(int cus, const ws::AttnArgs &a, int64_t groups, int deal, ws::Til
     const int64_t items = (((int64_t)a.per_group + (1 << deal) - 1) >> deal << deal) * groups;
     const int64_t none = items - a.n_work;
     // a causal item's mean tiles, in hundredths (as in plan_prefill)
-    const int64_t mean = shape.kg == 2 ? 56 * (a.nqt + 1) + 350 : 200 * (a.nqt + 1) + 250;
+    const int64_t mean = shape.kg == 2 ? 53 * (a.nqt + 1) + 300 : 200 * (a.nqt + 1) + 250;
     return items <= cus || (items <= (int64_t)1 << 22 && 20 * 200 * none <= mean * a.n_work);
 }
 

@@ -57,7 +57,11 @@ def test_prefill_of_small_groups_launches_its_items_only(batch, hq, hkv, seq):
     (1, 8, 8, 1000, 1000, 2),     # both fit one round: the shorter items win
     (3, 12, 4, 1000, 40, 2),      # nearly causal: the longest items are few
     (1, 32, 8, 1100, 100, 2),
+    (3, 8, 8, 3075, 190, 2),      # 75 items on 32 units a XCD
+    (5, 16, 4, 956, 956, 1),
     (1, 40, 8, 3300, 200, 1),
+    (1, 8, 8, 192, 192, 1),
+    (1, 64, 8, 2686, 1343, 1),    # 2.75 rounds
 ])
 def test_prefill_tile_follows_the_blocks(batch, hq, hkv, seq, block, groups):
     """The 128-row tile is chosen by the keys the rows really see: taken as
